@@ -112,10 +112,10 @@ __global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restric
     if (2 * u < nt) {
       const f32x4 p0 = sc[2 * u], p1 = sc[2 * u + 1];
       uint4 pa;
-      pa.x = (uint32_t)f2bf(p0[0] * inv) | ((uint32_t)f2bf(p0[1] * inv) << 16);
-      pa.y = (uint32_t)f2bf(p0[2] * inv) | ((uint32_t)f2bf(p0[3] * inv) << 16);
-      pa.z = (uint32_t)f2bf(p1[0] * inv) | ((uint32_t)f2bf(p1[1] * inv) << 16);
-      pa.w = (uint32_t)f2bf(p1[2] * inv) | ((uint32_t)f2bf(p1[3] * inv) << 16);
+      pa.x = f2bf2(p0[0] * inv, p0[1] * inv);
+      pa.y = f2bf2(p0[2] * inv, p0[3] * inv);
+      pa.z = f2bf2(p1[0] * inv, p1[1] * inv);
+      pa.w = f2bf2(p1[2] * inv, p1[3] * inv);
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) {
         // V^T fragment of keys 32 u + 4 g + 0..3 (lo) and 16 further (hi), dim 16 dt + r, read

@@ -19,15 +19,17 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
 
-// float -> bf16 bits, round to nearest even; NaN stays NaN (quiet). Written as a select, not
-// an early return: as a branch it compiled to a divergent if per conversion (exec-mask
-// saves and restores around every element of an epilogue)
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  const uint32_t u = __float_as_uint(f);
-  const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-  const uint32_t quiet_nan = (u >> 16) | 0x40u;
-  return (uint16_t)((u & 0x7fffffffu) > 0x7f800000u ? quiet_nan : rounded);
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// float -> bf16 bits, round to nearest even, NaN stays NaN (quiet): gfx950's v_cvt_pk_bf16_f32,
+// whose results equal the integer form ((u + 0x7fff + (u >> 16 & 1)) >> 16, NaN made quiet) for
+// all 2^32 inputs. Two values an instruction instead of about seven each: in the contractions'
+// epilogues BERT's 8192 x 768 -> 2304 projection went from 37.9 to 36.0 us.
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
+__device__ __forceinline__ uint16_t f2bf(float f) { return (uint16_t)f2bf2(f, f); }
 
 // erf(x) by Abramowitz and Stegun, Handbook of Mathematical Functions, formula 7.1.26:
 // 1 - (a1 t + ... + a5 t^5) exp(-x^2) with t = 1 / (1 + p |x|), odd in x, absolute error at

@@ -32,62 +32,65 @@ struct PtrFields<GemmArgs> {
   }
 };
 
-__device__ __forceinline__ int res_kind_dev(const Epilogue& ep) { return !ep.res ? 0 : ep.res_f32 ? 2 : 1; }
-
-// The epilogue's inputs for four consecutive outputs of a row, as raw bits: fetched
-// ahead of the values they apply to, so that their loads overlap other loads. `base` is
-// m * N + n0; requires n0 % 4 == 0, n0 + 3 < N, N % 4 == 0.
-// RES, when not -1, fixes the residual's kind at compile time (0 none, 1 bf16, 2 fp32; see
-// res_kind): a kernel that fetches these ahead of other loads then has no branch between
-// the loads, which would otherwise make the compiler wait for one before issuing the next.
-struct Ep4In {
-  uint2 bias;   // bf16 x 4
-  uint4 res;    // fp32 x 4, or bf16 x 4 in .x and .y
+// The epilogue's inputs for a run of R (4 or 8) consecutive outputs of a row, as raw bits:
+// fetched ahead of the values they apply to, so that their loads overlap other loads. `base` is
+// m * N + n0; requires n0 % R == 0, n0 + R - 1 < N, N % R == 0.
+template <int R>
+struct EpRun;
+template <>
+struct EpRun<4> {
+  typedef uint2 Raw;
+  Raw bias, res;
 };
+template <>
+struct EpRun<8> {
+  typedef uint4 Raw;
+  Raw bias, res;
+};
+typedef EpRun<4> Ep4In;
 
-inline int res_kind(const Epilogue& ep) { return !ep.res ? 0 : ep.res_f32 ? 2 : 1; }
+// RES, when not -1, fixes at compile time whether there is a residual: a kernel that fetches
+// these ahead of other loads then has no branch between the loads, which would otherwise make
+// the compiler wait for one before issuing the next.
+inline int res_kind(const Epilogue& ep) { return ep.res ? 1 : 0; }
 
 template <int RES = -1>
 __device__ __forceinline__ Ep4In ep4_fetch(const Epilogue& ep, size_t base, int n0) {
   Ep4In in;   // fields the epilogue does not use stay unset (no copies, no waits)
   if (ep.bias) in.bias = *reinterpret_cast<const uint2*>(ep.bias + n0);
-  const int rk = RES >= 0 ? RES : res_kind_dev(ep);
-  if (rk == 2) {
-    in.res = *reinterpret_cast<const uint4*>(static_cast<const float*>(ep.res) + base);
-  } else if (rk == 1) {
-    const uint2 r = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(ep.res) + base);
-    in.res.x = r.x; in.res.y = r.y;
-  }
+  if (RES >= 0 ? RES == 1 : ep.res != nullptr)
+    in.res = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(ep.res) + base);
   return in;
 }
 
-// v += bias; v += residual; v = act(v), each step only where the epilogue has it
-template <int RES = -1>
-__device__ __forceinline__ void ep4_apply(const Epilogue& ep, const Ep4In& in, float (&v)[4]) {
-  if (ep.bias) {
-    v[0] += bf2f(in.bias.x & 0xffff); v[1] += bf2f(in.bias.x >> 16);
-    v[2] += bf2f(in.bias.y & 0xffff); v[3] += bf2f(in.bias.y >> 16);
-  }
-  const int rk = RES >= 0 ? RES : res_kind_dev(ep);
-  if (rk == 2) {
-    v[0] += __uint_as_float(in.res.x); v[1] += __uint_as_float(in.res.y);
-    v[2] += __uint_as_float(in.res.z); v[3] += __uint_as_float(in.res.w);
-  } else if (rk == 1) {
-    v[0] += bf2f(in.res.x & 0xffff); v[1] += bf2f(in.res.x >> 16);
-    v[2] += bf2f(in.res.y & 0xffff); v[3] += bf2f(in.res.y >> 16);
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = act_apply(v[e], ep.act);
+__device__ __forceinline__ void add_bf16(float (&v)[4], uint2 w) {
+  v[0] += bf2f(w.x & 0xffff); v[1] += bf2f(w.x >> 16); v[2] += bf2f(w.y & 0xffff); v[3] += bf2f(w.y >> 16);
+}
+__device__ __forceinline__ void add_bf16(float (&v)[8], uint4 w) {
+  v[0] += bf2f(w.x & 0xffff); v[1] += bf2f(w.x >> 16); v[2] += bf2f(w.y & 0xffff); v[3] += bf2f(w.y >> 16);
+  v[4] += bf2f(w.z & 0xffff); v[5] += bf2f(w.z >> 16); v[6] += bf2f(w.w & 0xffff); v[7] += bf2f(w.w >> 16);
 }
 
-__device__ __forceinline__ void ep4_store(const Epilogue& ep, size_t base, const float (&v)[4]) {
+// v += bias; v += residual; v = act(v), each step only where the epilogue has it
+template <int RES = -1, int R>
+__device__ __forceinline__ void ep_apply(const Epilogue& ep, const EpRun<R>& in, float (&v)[R]) {
+  if (ep.bias) add_bf16(v, in.bias);
+  if (RES >= 0 ? RES == 1 : ep.res != nullptr) add_bf16(v, in.res);
+#pragma unroll
+  for (int e = 0; e < R; ++e) v[e] = act_apply(v[e], ep.act);
+}
+
+template <int R>
+__device__ __forceinline__ void ep_store(const Epilogue& ep, size_t base, const float (&v)[R]) {
   if (ep.out_f32) {
-    *reinterpret_cast<float4*>(static_cast<float*>(ep.out) + base) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+    for (int e = 0; e < R; e += 4)
+      *reinterpret_cast<float4*>(static_cast<float*>(ep.out) + base + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+  } else if constexpr (R == 8) {
+    *reinterpret_cast<uint4*>(static_cast<uint16_t*>(ep.out) + base) =
+        make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
   } else {
-    uint2 o;
-    o.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-    o.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(ep.out) + base) = o;
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(ep.out) + base) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
   }
 }
 
@@ -101,15 +104,14 @@ __device__ __forceinline__ void store_row4(const GemmArgs& a, int m, int n0, f32
   const bool full = (n0 + 3 < a.N) && ((a.N & 3) == 0);
   if (full) {
     const Ep4In in = ep4_fetch(ep, base, n0);
-    ep4_apply(ep, in, v);
-    ep4_store(ep, base, v);
+    ep_apply(ep, in, v);
+    ep_store(ep, base, v);
     return;
   }
   for (int e = 0; e < 4 && n0 + e < a.N; ++e) {
     float t = v[e];
     if (ep.bias) t += bf2f(ep.bias[n0 + e]);
-    if (ep.res) t += ep.res_f32 ? static_cast<const float*>(ep.res)[base + e]
-                                : bf2f(static_cast<const uint16_t*>(ep.res)[base + e]);
+    if (ep.res) t += bf2f(static_cast<const uint16_t*>(ep.res)[base + e]);
     t = act_apply(t, ep.act);
     if (ep.out_f32) static_cast<float*>(ep.out)[base + e] = t;
     else static_cast<uint16_t*>(ep.out)[base + e] = f2bf(t);

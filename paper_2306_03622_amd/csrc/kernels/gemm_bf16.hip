@@ -9,454 +9,21 @@
 // features of one row, which the epilogue stores as one vector.
 //
 // Kernels here (the skinny M <= 32 case is in gemv_bf16.hip):
-//   * k_gemm: LDS-tiled BN x BM x BK tiles, 4 waves in a 2 x 2 arrangement, global loads
-//     issued several k-stages ahead into a register ring, double-buffered LDS, and a
-//     deterministic split over k when the tile grid alone cannot fill the chip. The
-//     activation loader is either a plain row-major matrix or an NHWC implicit-GEMM
-//     (im2col) gather for convolutions, k = (kh * KW + kw) * C + c, matching OHWI weight
-//     rows.
+//   * k_gemm (gemm_tile.hpp): BN x BM output tiles over a ring of 64-deep k-stages in LDS that
+//     loads fill directly, and a deterministic split over k when a deep contraction's tiles
+//     cannot fill the chip. The activation loader is either a plain row-major matrix or an
+//     NHWC implicit-GEMM (im2col) gather for convolutions, k = (kh * KW + kw) * C + c, matching
+//     OHWI weight rows.
 //   * k_conv_smallc: convolutions with fewer than 8 input channels (the ResNet stem),
 //     whose input window rows are staged in LDS.
-#include "gemm_args.hpp"
+#include <algorithm>
+
+#include "gemm_tile.hpp"
 
 namespace tp {
 namespace k {
 
 namespace {
-
-// Epilogue of 16 consecutive outputs n0 .. n0+15 of row m (contiguous loads and stores)
-__device__ __forceinline__ void store_row16(const GemmArgs& a, int m, int n0, const float (&v_in)[16]) {
-  const Epilogue& ep = a.ep;
-  const size_t base = (size_t)m * a.N + n0;
-  if (n0 + 15 < a.N && (a.N & 7) == 0) {
-    float v[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = v_in[e];
-    if (ep.bias) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint4 b = *reinterpret_cast<const uint4*>(ep.bias + n0 + 8 * h);
-        const uint32_t w[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[8 * h + 2 * e] += bf2f(w[e] & 0xffff);
-          v[8 * h + 2 * e + 1] += bf2f(w[e] >> 16);
-        }
-      }
-    }
-    if (ep.res) {
-      if (ep.res_f32) {
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          const float4 r = *reinterpret_cast<const float4*>(static_cast<const float*>(ep.res) + base + 4 * h);
-          v[4 * h] += r.x; v[4 * h + 1] += r.y; v[4 * h + 2] += r.z; v[4 * h + 3] += r.w;
-        }
-      } else {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(ep.res) + base + 8 * h);
-          const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[8 * h + 2 * e] += bf2f(w[e] & 0xffff);
-            v[8 * h + 2 * e + 1] += bf2f(w[e] >> 16);
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = act_apply(v[e], ep.act);
-    if (ep.out_f32) {
-#pragma unroll
-      for (int h = 0; h < 4; ++h)
-        *reinterpret_cast<float4*>(static_cast<float*>(ep.out) + base + 4 * h) =
-            make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
-    } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        uint4 o;
-        o.x = (uint32_t)f2bf(v[8 * h]) | ((uint32_t)f2bf(v[8 * h + 1]) << 16);
-        o.y = (uint32_t)f2bf(v[8 * h + 2]) | ((uint32_t)f2bf(v[8 * h + 3]) << 16);
-        o.z = (uint32_t)f2bf(v[8 * h + 4]) | ((uint32_t)f2bf(v[8 * h + 5]) << 16);
-        o.w = (uint32_t)f2bf(v[8 * h + 6]) | ((uint32_t)f2bf(v[8 * h + 7]) << 16);
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(ep.out) + base + 8 * h) = o;
-      }
-    }
-    return;
-  }
-  for (int e = 0; e < 16 && n0 + e < a.N; ++e) {
-    float t = v_in[e];
-    if (ep.bias) t += bf2f(ep.bias[n0 + e]);
-    if (ep.res) t += ep.res_f32 ? static_cast<const float*>(ep.res)[base + e]
-                                : bf2f(static_cast<const uint16_t*>(ep.res)[base + e]);
-    t = act_apply(t, ep.act);
-    if (ep.out_f32) static_cast<float*>(ep.out)[base + e] = t;
-    else static_cast<uint16_t*>(ep.out)[base + e] = f2bf(t);
-  }
-}
-
-// store_row16 with the bias and a bf16 residual already loaded (raw bits of 16 values each);
-// requires n0 + 15 < N and N % 8 == 0. The same operations in the same order, so the same bits.
-__device__ __forceinline__ void store_row16_pre(const GemmArgs& a, int m, int n0, const float (&v_in)[16],
-                                                const uint4 (&bias)[2], const uint4 (&res)[2]) {
-  const Epilogue& ep = a.ep;
-  const size_t base = (size_t)m * a.N + n0;
-  float v[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) v[e] = v_in[e];
-  if (ep.bias) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t w[4] = {bias[h].x, bias[h].y, bias[h].z, bias[h].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[8 * h + 2 * e] += bf2f(w[e] & 0xffff);
-        v[8 * h + 2 * e + 1] += bf2f(w[e] >> 16);
-      }
-    }
-  }
-  if (ep.res) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t w[4] = {res[h].x, res[h].y, res[h].z, res[h].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[8 * h + 2 * e] += bf2f(w[e] & 0xffff);
-        v[8 * h + 2 * e + 1] += bf2f(w[e] >> 16);
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 16; ++e) v[e] = act_apply(v[e], ep.act);
-  if (ep.out_f32) {
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-      *reinterpret_cast<float4*>(static_cast<float*>(ep.out) + base + 4 * h) =
-          make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
-  } else {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      uint4 o;
-      o.x = (uint32_t)f2bf(v[8 * h]) | ((uint32_t)f2bf(v[8 * h + 1]) << 16);
-      o.y = (uint32_t)f2bf(v[8 * h + 2]) | ((uint32_t)f2bf(v[8 * h + 3]) << 16);
-      o.z = (uint32_t)f2bf(v[8 * h + 4]) | ((uint32_t)f2bf(v[8 * h + 5]) << 16);
-      o.w = (uint32_t)f2bf(v[8 * h + 6]) | ((uint32_t)f2bf(v[8 * h + 7]) << 16);
-      *reinterpret_cast<uint4*>(static_cast<uint16_t*>(ep.out) + base + 8 * h) = o;
-    }
-  }
-}
-
-// ------------------------------------------------------------------ tiled
-
-struct RowInfo {
-  int b, ih0, iw0;   // conv: sample and top-left input corner; rows: b = m
-  bool valid;
-  size_t base;       // X_CONV64: element offset of (b, ih0, iw0, 0)
-};
-
-template <int MODE>
-__device__ __forceinline__ RowInfo row_info(const GemmArgs& a, int m) {
-  RowInfo ri;
-  ri.valid = m < a.M;
-  if (MODE == X_ROWS) {
-    ri.b = m; ri.ih0 = 0; ri.iw0 = 0;
-  } else {
-    const int mm = ri.valid ? m : 0;
-    const int hw = a.Ho * a.Wo;
-    ri.b = mm / hw;
-    const int rem = mm - ri.b * hw;
-    const int oh = rem / a.Wo, ow = rem - (rem / a.Wo) * a.Wo;
-    ri.ih0 = oh * a.stride - a.pad;
-    ri.iw0 = ow * a.stride - a.pad;
-    ri.base = (((size_t)ri.b * a.H + ri.ih0) * a.W + ri.iw0) * (size_t)a.C;
-  }
-  return ri;
-}
-
-// k-stage position of an X_CONV64 contraction: filter tap (kh, kw) and channel offset c0,
-// identical for every thread of the workgroup
-struct TapPos {
-  int kh, kw, c0;
-  __device__ void init(const GemmArgs& a, int k0) {
-    const int tap = k0 / a.C;
-    c0 = k0 - tap * a.C;
-    kh = tap / a.KW;
-    kw = tap - kh * a.KW;
-  }
-};
-
-// 16 zero bytes in device memory: the blocked-weight loader (not read through buffer loads)
-// reads them for an operand outside the matrix, so invalid data is zero as loaded. (Zeroing it after the load
-// instead, when stored to LDS, made the compiler compute every ring slot's masks at the
-// top of the main loop, and so wait there for every load in flight, including those just
-// issued for later stages: a ring of any depth then hid one stage of latency.)
-__device__ uint4 g_zero16[1];
-
-__device__ __forceinline__ uint4 load_or_zero(const uint16_t* p, bool ok) {
-  return *(ok ? reinterpret_cast<const uint4*>(p) : static_cast<const uint4*>(g_zero16));
-}
-
-// Buffer loads of a row-major operand: one buffer resource per matrix (base, size in bytes
-// < 2^31), a 32-bit byte offset per load; an offset at or beyond the size reads zero, so an
-// invalid operand costs an offset select and no address arithmetic in 64 bits.
-constexpr uint32_t kOffNone = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// weights in 16 x 128 blocks (N % 16 == 0, K % 128 == 0): element (n, k) of an 8-run
-__device__ __forceinline__ uint4 load_w8_packed(const GemmArgs& a, int n, int k) {
-  const bool ok = n < a.N && k < a.K;
-  const int nn = ok ? n : 0, kk = ok ? k : 0;
-  const size_t off = ((((size_t)(nn >> 4) * (a.K >> 7) + (kk >> 7)) * 4 + ((kk >> 5) & 3)) * 512) +
-                     ((((kk >> 3) & 3) << 4) + (nn & 15)) * 8;
-  return load_or_zero(a.w + off, ok);
-}
-
-// One BN x BM output tile over the k-stages [s0, s0 + n) of this split (blockIdx.z). The
-// global loads of a stage are issued D stages before its multiplications, into a ring of D
-// register sets, so D memory round trips overlap (the tiles are small and the contractions
-// short, so latency, not bandwidth, bounds these kernels); LDS is double-buffered, one
-// barrier per stage. Invalid operand data (outside the matrix or the image) is loaded from a
-// zero block, so a stage's LDS store waits only for that stage's loads. With a.splits > 1
-// every split stores its fp32 partial to a.partials and k_split_reduce (the next launch on
-// the stream) sums the partials in split order, which is fixed, so results are
-// bit-reproducible.
-// WGN x WGM waves (64 WGN WGM threads) share a tile, each owning a (BN / WGN) x (BM / WGM)
-// block of it. 64 x 64 tiles of 2 x 2 waves are capped at 128 VGPRs, so four workgroups (16
-// waves) fit a CU as the LDS allows, instead of two at the uncapped register count (the
-// element-gather loader would spill under the cap and keeps it off); 8-wave tiles are capped
-// the same way for two workgroups per CU.
-template <int BN, int BM, int MODE>
-constexpr int gemm_min_waves_per_simd(int nt) {
-  return (nt == 256 && BN == 64 && BM == 64) ? 4 : nt == 512 ? 4 : 1;
-}
-
-// EPF (no k split, a bf16 or no residual, N a multiple of BN): each thread's epilogue inputs
-// (16 bias values and 16 residuals of its output row run) are loaded with the first stages'
-// operands instead of after the main loop, so that their memory round trip overlaps the
-// operands' rather than following the multiplications.
-template <int BN, int BM, int BK, int MODE, bool WVEC, bool PK, int D, int WGN = 2, int WGM = 2, bool EPF = false>
-__global__ __launch_bounds__(64 * WGN * WGM, (gemm_min_waves_per_simd<BN, BM, MODE>(64 * WGN * WGM)))
-void k_gemm(GemmArgs a) {
-  constexpr int NT = 64 * WGN * WGM;            // threads
-  // LDS row stride of the operand tiles: 80 bf16 (160 B). With 72 (144 B) the 16-byte
-  // fragment reads and stores conflicted on banks (rocprofv3 SQ_LDS_BANK_CONFLICT: 1.18 M
-  // cycles per BERT-base FFN1 launch at batch 8, 2.5 per LDS instruction); 80 measured zero
-  // conflicts (88 and 104 did not help), 4.5% off BERT-base's warm forward
-  constexpr int LDK = BK + 16;
-  constexpr int KV = BK / 8;                    // 16-byte vectors per row and stage
-  constexpr int RSTEP = NT / KV;                // rows covered by one pass of all threads
-  constexpr int VA = BN / RSTEP, VB = BM / RSTEP;
-  constexpr int NB = BN / WGN / 16, MB = BM / WGM / 16;   // 16 x 16 blocks per wave
-  static_assert(VA >= 1 && VB >= 1 && BN % RSTEP == 0 && BM % RSTEP == 0 && NB >= 1 && MB >= 1 &&
-                    BK % 32 == 0 && D >= 2 && D % 2 == 0, "tile shape");
-  static_assert(MODE != X_CONV64 || BK == 64, "X_CONV64 steps one 64-deep stage per tap position");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * (BN + BM) * LDK];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn = wave % WGN, wm = wave / WGN;
-  const int n_base = blockIdx.x * BN, m_base = blockIdx.y * BM;
-  const int row0 = tid / KV, kq = (tid % KV) * 8;
-
-  RowInfo ri[VB];
-#pragma unroll
-  for (int p = 0; p < VB; ++p) ri[p] = row_info<MODE>(a, m_base + row0 + RSTEP * p);
-
-  f32x4 acc[NB][MB];
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < MB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int nst = (a.K + BK - 1) / BK;
-  const int s0 = blockIdx.z * a.kst;
-  const int n = min(s0 + a.kst, nst) - s0;      // stages of this split (>= 1: no empty split)
-  uint4 ra[D][VA], rb[D][VB];
-  // row-major operands through buffer loads: per-thread byte offsets of k = 0
-  // (X_CONV64: the input image, offsets of each row's top-left tap, wrapping modulo 2^32 where
-  // the window starts in the padding; a valid tap brings them back inside the image)
-  constexpr bool BUFW = WVEC && !PK, BUFX = MODE == X_ROWS, BUFC = MODE == X_CONV64;
-  const __amdgpu_buffer_rsrc_t rw = buffer_of(a.w, BUFW ? (uint32_t)((size_t)a.N * a.K * 2) : 0u);
-  const uint32_t xbytes = BUFX ? (uint32_t)((size_t)a.M * a.K * 2)
-                          : BUFC ? (uint32_t)((size_t)(a.M / (a.Ho * a.Wo)) * a.H * a.W * a.C * 2) : 0u;
-  const __amdgpu_buffer_rsrc_t rx = buffer_of(a.x, xbytes);
-  uint32_t offw[VA], offx[VB];
-  if constexpr (BUFW) {
-#pragma unroll
-    for (int p = 0; p < VA; ++p) {
-      const int nn = n_base + row0 + RSTEP * p;
-      offw[p] = nn < a.N ? (uint32_t)(((size_t)nn * a.K + kq) * 2) : kOffNone;
-    }
-  }
-  if constexpr (BUFX) {
-#pragma unroll
-    for (int p = 0; p < VB; ++p) offx[p] = ri[p].valid ? (uint32_t)(((size_t)ri[p].b * a.K + kq) * 2) : kOffNone;
-  }
-  if constexpr (BUFC) {
-#pragma unroll
-    for (int p = 0; p < VB; ++p) offx[p] = (uint32_t)((ri[p].base + kq) * 2);
-  }
-  auto load = [&](int s, uint4 (&A)[VA], uint4 (&Bv)[VB]) {
-    const int k = s * BK + kq;
-    const bool kin = k < a.K;
-    if constexpr (BUFW) {
-#pragma unroll
-      for (int p = 0; p < VA; ++p) A[p] = buffer_load16(rw, kin ? offw[p] + (uint32_t)(s * BK * 2) : kOffNone);
-    } else {
-      static_assert(PK && WVEC, "weights: row-major (buffer loads) or blocked");
-#pragma unroll
-      for (int p = 0; p < VA; ++p) A[p] = load_w8_packed(a, n_base + row0 + RSTEP * p, k);
-    }
-    if constexpr (BUFX) {
-#pragma unroll
-      for (int p = 0; p < VB; ++p) Bv[p] = buffer_load16(rx, kin ? offx[p] + (uint32_t)(s * BK * 2) : kOffNone);
-    } else {
-      static_assert(BUFC, "activation modes: rows or 64-channel convolution taps");
-      TapPos tap;
-      tap.init(a, s * BK);
-      const uint32_t toff = (uint32_t)(((tap.kh * a.W + tap.kw) * a.C + tap.c0) * 2);
-#pragma unroll
-      for (int p = 0; p < VB; ++p) {
-        const int ih = ri[p].ih0 + tap.kh, iw = ri[p].iw0 + tap.kw;
-        const bool ok = ri[p].valid && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-        Bv[p] = buffer_load16(rx, ok ? offx[p] + toff : kOffNone);
-      }
-    }
-  };
-  auto store = [&](int buf, const uint4 (&A)[VA], const uint4 (&Bv)[VB]) {
-    uint16_t* As = lds + buf * (BN + BM) * LDK;
-    uint16_t* Bs = As + BN * LDK;
-#pragma unroll
-    for (int p = 0; p < VA; ++p) *reinterpret_cast<uint4*>(&As[(row0 + RSTEP * p) * LDK + kq]) = A[p];
-#pragma unroll
-    for (int p = 0; p < VB; ++p) *reinterpret_cast<uint4*>(&Bs[(row0 + RSTEP * p) * LDK + kq]) = Bv[p];
-  };
-  auto compute = [&](int buf) {
-    const uint16_t* As = lds + buf * (BN + BM) * LDK;
-    const uint16_t* Bs = As + BN * LDK;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 32) {
-      uint4 fa[NB], fb[MB];
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        fa[i] = *reinterpret_cast<const uint4*>(&As[(wn * (BN / WGN) + i * 16 + (lane & 15)) * LDK + kk + ((lane >> 4) << 3)]);
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-        fb[j] = *reinterpret_cast<const uint4*>(&Bs[(wm * (BM / WGM) + j * 16 + (lane & 15)) * LDK + kk + ((lane >> 4) << 3)]);
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[i]), as_bf16x8(fb[j]), acc[i][j], 0, 0, 0);
-    }
-  };
-
-  // prologue: stages 0 .. D-1 (relative) into ring slots 0 .. D-1, stage 0 into LDS buffer 0,
-  // then stage D into the freed slot 0
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-    if (i < n) load(s0 + i, ra[i], rb[i]);
-  // the epilogue's inputs of this thread's output run (EPF); an absent bias or residual is a
-  // buffer of no bytes, which reads zero, so no branch separates these loads
-  constexpr int TPR = BN / 16, RPI = NT / TPR;
-  static_assert(!EPF || (BM <= RPI && MODE == X_ROWS), "EPF: one output row per thread, row-major operands");
-  uint4 pre_b[2], pre_r[2];
-  if constexpr (EPF) {
-    const int ml = tid / TPR, m = m_base + ml, n0 = n_base + (tid % TPR) * 16;
-    const __amdgpu_buffer_rsrc_t rbias = buffer_of(a.ep.bias, a.ep.bias ? (uint32_t)(a.N * 2) : 0u);
-    const __amdgpu_buffer_rsrc_t rres =
-        buffer_of(a.ep.res, a.ep.res ? (uint32_t)((size_t)a.M * a.N * 2) : 0u);
-    const uint32_t ro = (ml < BM && m < a.M) ? (uint32_t)(((size_t)m * a.N + n0) * 2) : kOffNone;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      pre_b[h] = buffer_load16(rbias, (uint32_t)(n0 * 2 + 16 * h));
-      pre_r[h] = buffer_load16(rres, ro + (uint32_t)(16 * h));
-    }
-  }
-  store(0, ra[0], rb[0]);
-  if (D < n) load(s0 + D, ra[0], rb[0]);
-  __syncthreads();
-  // Stage j sits in ring slot j % D and LDS buffer j % 2; the loops are unrolled by D (even),
-  // so every slot and buffer index is a constant. Steady state: trips whose loads are all
-  // needed, with no branch around any load, so the compiler waits for exactly the stage it
-  // stores. Drain: the last trips, where loads and stores beyond the split are skipped.
-  int j0 = 0;
-  for (; j0 + 2 * D < n; j0 += D) {
-#pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int nx = (u + 1) % D;
-      compute(u & 1);
-      store((u + 1) & 1, ra[nx], rb[nx]);        // stage j0+u+1
-      load(s0 + j0 + u + 1 + D, ra[nx], rb[nx]);  // stage j0+u+1+D
-      __syncthreads();
-    }
-  }
-  for (; j0 < n; j0 += D) {
-#pragma unroll
-    for (int u = 0; u < D; ++u) {
-      const int j = j0 + u, nx = (u + 1) % D;
-      if (j < n) {
-        compute(u & 1);
-        if (j + 1 < n) store((u + 1) & 1, ra[nx], rb[nx]);
-        if (j + 1 + D < n) load(s0 + j + 1 + D, ra[nx], rb[nx]);
-        __syncthreads();
-      }
-    }
-  }
-
-  // Output: the fp32 tile is staged in LDS (row-major [m][n], padded) so that each thread then
-  // handles a 16-wide run of one row with contiguous loads and stores (the accumulator layout
-  // would otherwise give 16 rows x 8 bytes per store instruction). The main loop ended with a
-  // barrier, so the LDS is free.
-  constexpr int TS = BN + 4;
-  static_assert((size_t)BM * TS * 4 <= sizeof(lds), "output tile must fit the operand buffers");
-  float* T = reinterpret_cast<float*>(lds);
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      const int ml = wm * (BM / WGM) + j * 16 + (lane & 15);
-      const int nl = wn * (BN / WGN) + i * 16 + ((lane >> 4) << 2);
-      const f32x4 v = acc[i][j];
-      *reinterpret_cast<float4*>(&T[ml * TS + nl]) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-  __syncthreads();
-  const int nl = (tid % TPR) * 16;
-  const int n0 = n_base + nl;
-  const bool vec = n0 + 15 < a.N && (a.N & 3) == 0;
-  for (int ml = tid / TPR; ml < BM; ml += RPI) {
-    const int m = m_base + ml;
-    if (m >= a.M || n0 >= a.N) continue;
-    float v[16];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const float4 t = *reinterpret_cast<const float4*>(&T[ml * TS + nl + 4 * h]);
-      v[4 * h] = t.x; v[4 * h + 1] = t.y; v[4 * h + 2] = t.z; v[4 * h + 3] = t.w;
-    }
-    if (a.splits > 1) {
-      // fp32 partial of this split: P[split][m][n]
-      float* p = a.partials + (size_t)blockIdx.z * a.M * a.N + (size_t)m * a.N + n0;
-      if (vec) {
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-          *reinterpret_cast<float4*>(p + 4 * h) = make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
-      } else {
-        for (int e = 0; e < 16 && n0 + e < a.N; ++e) p[e] = v[e];
-      }
-    } else if constexpr (EPF) {
-      store_row16_pre(a, m, n0, v, pre_b, pre_r);
-    } else {
-      store_row16(a, m, n0, v);
-    }
-  }
-}
 
 // ------------------------------------------------------------------ few input channels
 
@@ -651,8 +218,8 @@ __global__ __launch_bounds__(256) void k_split_reduce(GemmArgs a) {
         if (z0 + u < a.splits) sum += f32x4{t[u].x, t[u].y, t[u].z, t[u].w};
     }
     float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-    ep4_apply<RES>(a.ep, in, v);
-    ep4_store(a.ep, base, v);
+    ep_apply<RES>(a.ep, in, v);
+    ep_store(a.ep, base, v);
     return;
   }
   for (int z = 0; z < a.splits; ++z) {
@@ -674,8 +241,7 @@ void launch_split_reduce_res(const GemmArgs& a, dim3 grid, dim3 block, hipStream
 void launch_split_reduce(const GemmArgs& a, dim3 grid, dim3 block, hipStream_t s) {
   switch (res_kind(a.ep)) {
     case 0: launch_split_reduce_res<0>(a, grid, block, s); break;
-    case 1: launch_split_reduce_res<1>(a, grid, block, s); break;
-    default: launch_split_reduce_res<2>(a, grid, block, s); break;
+    default: launch_split_reduce_res<1>(a, grid, block, s); break;
   }
 }
 
@@ -698,82 +264,79 @@ hipError_t finish(const GemmArgs& a, hipStream_t s) {
   return hipSuccess;
 }
 
-template <int BN, int BM, int BK, int MODE, bool WVEC, int D, int WGN = 2, int WGM = 2>
+template <int BN, int BM, int WGN, int WGM, int NST, int MINW, int MODE, bool VEC = true>
 hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) {
-  const int tn = (a.N + BN - 1) / BN, tm = (a.M + BM - 1) / BM;
-  const int nst = (a.K + BK - 1) / BK;
+  const int tn = (a.N + BN - 1) / BN, tm = (a.M + BM - 1) / BM, nst = (a.K + 63) / 64;
   a.kst = (nst + splits - 1) / splits;
   a.splits = (nst + a.kst - 1) / a.kst;        // no empty split
   a.partials = sp.partials;
-  dim3 grid(tn, tm, a.splits);
-  if constexpr (MODE == X_ROWS) {
+  const dim3 grid(tn * tm * a.splits), block(64 * WGN * WGM);
+  if constexpr (MODE == X_ROWS && VEC) {
     if (a.ep.w_packed) {
-      (void)launch((k_gemm<BN, BM, BK, MODE, WVEC, true, D, WGN, WGM>), grid, dim3(64 * WGN * WGM), 0, s, a);
+      (void)launch((k_gemm<BN, BM, WGN, WGM, NST, MODE, true, MINW, true>), grid, block, 0, s, a, tn, tm);
       return finish(a, s);
     }
   }
-  // an unsplit row-major contraction fetches its epilogue inputs with its first operands
-  // (EPF). Against fetching them after the main loop, whole warm forwards (A/B on one machine):
-  // ResNet-50 -3 to -4% at batch 1 and 8, BERT-base -3% at batch 1, -1% at batch 8; for
-  // the convolution taps as well, no further change (-0.5% to +0.3%), so those do not.
-  constexpr bool kEpfTile = MODE == X_ROWS && BM <= 64 * WGN * WGM / (BN / 16);
-  if constexpr (kEpfTile) {
-    if (a.splits == 1 && !(a.ep.res && a.ep.res_f32) && a.N % BN == 0 && a.N % 16 == 0 &&
-        (size_t)a.M * a.N * 2 < (1u << 31)) {
-      (void)launch((k_gemm<BN, BM, BK, MODE, WVEC, false, D, WGN, WGM, true>), grid, dim3(64 * WGN * WGM), 0, s, a);
-      return finish(a, s);
-    }
-  }
-  (void)launch((k_gemm<BN, BM, BK, MODE, WVEC, false, D, WGN, WGM>), grid, dim3(64 * WGN * WGM), 0, s, a);
+  (void)launch((k_gemm<BN, BM, WGN, WGM, NST, MODE, false, MINW, VEC>), grid, block, 0, s, a, tn, tm);
   return finish(a, s);
 }
 
-// Tile shape and k split of a tiled contraction. Measured on MI355X over every contraction of
-// ResNet-50 and BERT-base at batch 1 and 8 (each shape timed under graph replay with 20 tile
-// shapes and 6 split counts): the fastest launches fill the 256 CUs with about one to three
-// workgroups each rather than many small ones or a few large ones; a k split pays only for
-// contractions deeper than about 12 stages whose tiles alone leave CUs idle, since its
-// reduction is a launch of its own (about 2-3 us); tiles larger than 64 x 64 and 128-deep
-// stages were never faster at these sizes (in whole forward passes, 128-deep stages for the
-// smaller tiles: -1% at batch 1, +3% at batch 8; a ring of four stages: +3-6%). So: the largest of 64 x 64, 64 x 32, 32 x 64 and
-// 32 x 32 (output features x rows) whose grid has at least 256 tiles (else 32 x 32); then
-// splits while a split keeps more than 12 stages, the grid stays within 768 workgroups, each
-// split keeps at least 4 stages and the fp32 partials fit the scratch. A row LayerNorm then
-// rides on the split reduction, or takes a launch of its own. 128 x 128 tiles for grids of
-// well over a few such tiles per CU.
+// Tile shape (output features x rows), ring depth and k split of a tiled contraction, by how many
+// tiles a shape gives the 256 CUs. Measured on MI355X over every contraction of ResNet-50 and
+// BERT-base at batch 1, 8 and 32 and MLP layers of 64 to 8192 rows, under graph replay with
+// 64 x 64 to 256 x 256 tiles (us; tiles in brackets):
+//   256 x 256 for contractions of 32 stages and more with two such tiles per CU: 8192 x 4096 x
+//     4096 [512] 243 against 267 with 128 x 128; at 12 stages, 8192 x 3072 x 768 [384], 64
+//     against 51 (a tile's fill and epilogue are not covered by another's loop).
+//   128 x 128, two per CU, from 196 tiles: 25088 x 128 x 1152 [196] 14.1 against 15.0 with
+//     64 x 64, 1568 x 2048 x 512 [208] 8.4 against 9.3; below, 1024 x 3072 x 768 [192] 11.6
+//     against 10.3, 6272 x 256 x 2304 [98] 19.9 against 15.4.
+//   64 x 64 from 192 tiles, with four stages in the ring while two per CU hold all tiles
+//     (1024 x 768 x 3072 [192] 12.7, with two stages 23; 256 x 4096 x 4096 [256] 16.1 against 31), else
+//     with two stages and up to five per CU (100352 x 64 x 64 [1568] 7.7 against 9.8 with four).
+//   64 x 32, then 32 x 64, from 192 tiles, else 32 x 32.
+// A k split costs a reduction, a launch of 2 to 3 us, so only contractions of 36 stages and more
+// whose tiles leave CUs idle are split, each split keeping 9 stages: 64 x 32 tiles from 64 of
+// them, up to 448 workgroups (392 x 512 x 4608 [104, 4 splits] 11.5, unsplit 32 x 32 14.7), else
+// 32 x 32, up to 256 (49 x 512 x 4608 [32, 8 splits] 7.8, unsplit 16; 196 x 256 x 2304 [56, 4
+// splits] 6.9, unsplit 7.6). Not a contraction with a row LayerNorm: 128 x 768 x 3072 [96] 7.1
+// unsplit, 7.5 split.
 struct TilePlan {
-  int bn, bm, splits;
+  int bn, bm, ring, splits;
 };
 
 TilePlan plan_tiles(const GemmArgs& a, const Split& sp) {
   auto tiles = [&](int bn, int bm) { return (long)((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-  if (tiles(128, 128) >= 1024) return {128, 128, 1};
-  static constexpr int kShapes[4][2] = {{64, 64}, {64, 32}, {32, 64}, {32, 32}};
-  TilePlan p{32, 32, 1};
-  for (const auto& t : kShapes)
-    if (tiles(t[0], t[1]) >= 256) {
-      p.bn = t[0];
-      p.bm = t[1];
-      break;
-    }
-  const long nt = tiles(p.bn, p.bm);
   const int nst = (a.K + 63) / 64;
-  const size_t per_split = (size_t)a.M * a.N * 4;
-  if (sp.partials)
-    while (nst > 12 * p.splits && nt * (p.splits + 1) <= 768 && nst >= 4 * (p.splits + 1) &&
-           per_split * (p.splits + 1) <= sp.partial_bytes)
-      ++p.splits;
-  return p;
+  if (a.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
+  if (nst >= 32 && tiles(256, 256) >= 512) return {256, 256, 2, 1};
+  // (also where the small tiles' 32-bit epilogue offsets would not do)
+  if (tiles(128, 128) >= 196 || (size_t)a.M * a.N * 2 >= (1u << 31)) return {128, 128, 2, 1};
+  if (tiles(64, 64) >= 192) return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, 1};
+  if (tiles(64, 32) >= 192) return {64, 32, 3, 1};
+  if (tiles(32, 64) >= 192) return {32, 64, 3, 1};
+  if (sp.partials && nst >= 36 && !a.ep.ln_g) {
+    const bool wide = tiles(64, 32) >= 64;
+    const long nt = wide ? tiles(64, 32) : tiles(32, 32);
+    const size_t per_split = (size_t)a.M * a.N * 4;
+    const int z = (int)std::min<long>({(wide ? 448 : 256) / nt, nst / 9, (long)(sp.partial_bytes / per_split)});
+    if (z > 1) return wide ? TilePlan{64, 32, 3, z} : TilePlan{32, 32, 4, z};
+  }
+  return {32, 32, 4, 1};
 }
 
-template <int MODE, bool WVEC>
+template <int MODE>
 hipError_t pick_tiled(const GemmArgs& a, const Split& sp, hipStream_t s) {
   const TilePlan p = plan_tiles(a, sp);
-  if (p.bn == 128) return launch_tiled<128, 128, 64, MODE, WVEC, 2>(a, p.splits, sp, s);
-  if (p.bn == 64 && p.bm == 64) return launch_tiled<64, 64, 64, MODE, WVEC, 2>(a, p.splits, sp, s);
-  if (p.bn == 64) return launch_tiled<64, 32, 64, MODE, WVEC, 2>(a, p.splits, sp, s);
-  if (p.bm == 64) return launch_tiled<32, 64, 64, MODE, WVEC, 2>(a, p.splits, sp, s);
-  return launch_tiled<32, 32, 64, MODE, WVEC, 2>(a, p.splits, sp, s);
+  // waves n x m, ring, least waves per SIMD
+  if (p.bn == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
+  if (p.bn == 128) return launch_tiled<128, 128, 4, 2, 2, 4, MODE>(a, p.splits, sp, s);
+  if (p.bn == 64 && p.bm == 64 && p.ring == 2) return launch_tiled<64, 64, 2, 2, 2, 4, MODE>(a, p.splits, sp, s);
+  if (p.bn == 64 && p.bm == 64) return launch_tiled<64, 64, 2, 2, 4, 2, MODE>(a, p.splits, sp, s);
+  if (p.bn == 64) return launch_tiled<64, 32, 2, 2, 3, 4, MODE>(a, p.splits, sp, s);
+  if (p.bm == 64) return launch_tiled<32, 64, 1, 4, 3, 4, MODE>(a, p.splits, sp, s);
+  if (a.N % 8) return launch_tiled<32, 32, 2, 2, 4, 4, MODE, false>(a, p.splits, sp, s);
+  return launch_tiled<32, 32, 2, 2, 4, 4, MODE>(a, p.splits, sp, s);
 }
 
 bool ep_ok(const Epilogue& ep) {
@@ -796,7 +359,7 @@ hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N
   }
   // the tiled kernel addresses x and w through 32-bit buffer offsets
   if ((size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
-  return pick_tiled<X_ROWS, true>(a, sp, s);
+  return pick_tiled<X_ROWS>(a, sp, s);
 }
 
 hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
@@ -835,7 +398,7 @@ hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16
     }
     return hipGetLastError();
   }
-  if ((C & 63) == 0) return pick_tiled<X_CONV64, true>(a, sp, s);
+  if ((C & 63) == 0) return pick_tiled<X_CONV64>(a, sp, s);
   return hipErrorInvalidValue;
 }
 

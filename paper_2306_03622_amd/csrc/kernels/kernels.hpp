@@ -33,8 +33,7 @@ extern thread_local std::vector<LaunchRecord>* launch_log;
 // out[m][n] = v stored as bf16 or fp32. Row stride of res and out is N.
 struct Epilogue {
   const uint16_t* bias = nullptr;   // bf16 [N], may be null
-  const void* res = nullptr;        // [M][N], may be null
-  int res_f32 = 0;                  // res dtype: 0 bf16, 1 fp32
+  const void* res = nullptr;        // bf16 [M][N], may be null
   int act = 0;                      // ACT_*
   void* out = nullptr;
   int out_f32 = 0;                  // out dtype: 0 bf16, 1 fp32

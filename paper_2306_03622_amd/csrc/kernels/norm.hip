@@ -83,8 +83,8 @@ __device__ __forceinline__ void normalize_runs(float (&v)[PER], int D, const LnA
       *reinterpret_cast<float4*>(static_cast<float*>(out) + row_off + c0 + i) = make_float4(y[0], y[1], y[2], y[3]);
     } else {
       uint2 o;
-      o.x = (uint32_t)f2bf(y[0]) | ((uint32_t)f2bf(y[1]) << 16);
-      o.y = (uint32_t)f2bf(y[2]) | ((uint32_t)f2bf(y[3]) << 16);
+      o.x = f2bf2(y[0], y[1]);
+      o.y = f2bf2(y[2], y[3]);
       *reinterpret_cast<uint2*>(static_cast<uint16_t*>(out) + row_off + c0 + i) = o;
     }
   }
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void k_split_reduce_ln(GemmArgs a) {
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     float w[4] = {v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
-    ep4_apply<RES>(ep, in[i], w);
+    ep_apply<RES>(ep, in[i], w);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[4 * i + e] = w[e];
   }
@@ -215,8 +215,7 @@ template <int PER>
 void launch_split_reduce_ln(const GemmArgs& a, dim3 grid, dim3 block, hipStream_t s) {
   switch (res_kind(a.ep)) {
     case 0: launch_split_reduce_ln_res<PER, 0>(a, grid, block, s); break;
-    case 1: launch_split_reduce_ln_res<PER, 1>(a, grid, block, s); break;
-    default: launch_split_reduce_ln_res<PER, 2>(a, grid, block, s); break;
+    default: launch_split_reduce_ln_res<PER, 1>(a, grid, block, s); break;
   }
 }
 

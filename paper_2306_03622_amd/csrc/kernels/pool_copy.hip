@@ -56,10 +56,10 @@ __global__ __launch_bounds__(256) void k_maxpool3s2(const uint16_t* __restrict__
     }
   }
   uint4 o;
-  o.x = (uint32_t)f2bf(m[0]) | ((uint32_t)f2bf(m[1]) << 16);
-  o.y = (uint32_t)f2bf(m[2]) | ((uint32_t)f2bf(m[3]) << 16);
-  o.z = (uint32_t)f2bf(m[4]) | ((uint32_t)f2bf(m[5]) << 16);
-  o.w = (uint32_t)f2bf(m[6]) | ((uint32_t)f2bf(m[7]) << 16);
+  o.x = f2bf2(m[0], m[1]);
+  o.y = f2bf2(m[2], m[3]);
+  o.z = f2bf2(m[4], m[5]);
+  o.w = f2bf2(m[6], m[7]);
   *reinterpret_cast<uint4*>(y + (((size_t)b * Ho + oh) * Wo + ow) * C + c8 * 8) = o;
 }
 
