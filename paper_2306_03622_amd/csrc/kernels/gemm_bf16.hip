@@ -284,13 +284,11 @@ hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) 
 // Tile shape (output features x rows), ring depth and k split of a tiled contraction, by how many
 // tiles a shape gives the 256 CUs. Measured on MI355X over every contraction of ResNet-50 and
 // BERT-base at batch 1, 8 and 32 and MLP layers of 64 to 8192 rows, under graph replay with
-// 64 x 64 to 256 x 256 tiles (us; tiles in brackets):
-//   256 x 256 for contractions of 32 stages and more with two such tiles per CU: 8192 x 4096 x
-//     4096 [512] 243 against 267 with 128 x 128; at 12 stages, 8192 x 3072 x 768 [384], 64
-//     against 51 (a tile's fill and epilogue are not covered by another's loop).
+// 32 x 32 to 256 x 256 tiles (us; tiles in brackets):
 //   128 x 128, two per CU, from 196 tiles: 25088 x 128 x 1152 [196] 14.1 against 15.0 with
 //     64 x 64, 1568 x 2048 x 512 [208] 8.4 against 9.3; below, 1024 x 3072 x 768 [192] 11.6
 //     against 10.3, 6272 x 256 x 2304 [98] 19.9 against 15.4.
+//     From 16 stages on, 256 x 256 or 256 x 128 instead where large_tile_us says so.
 //   64 x 64 from 192 tiles, with four stages in the ring while two per CU hold all tiles
 //     (1024 x 768 x 3072 [192] 12.7, with two stages 23; 256 x 4096 x 4096 [256] 16.1 against 31), else
 //     with two stages and up to five per CU (100352 x 64 x 64 [1568] 7.7 against 9.8 with four).
@@ -305,13 +303,36 @@ struct TilePlan {
   int bn, bm, ring, splits;
 };
 
+// Time of a contraction with large tiles, a model fitted to the rates measured on MI355X. A round
+// of the chip (512 tiles of 128 x 128, two per CU, else 256) costs a rate per stage and a fixed
+// part, larger with a GELU; a last round of 128 x 128 tiles that leaves CUs with one tile costs
+// 0.66. Rows that are not whole 128-byte lines cost the smallest tiles, which load the most per
+// multiplication, 15%. Measured, us, with 128 x 128 / 256 x 128 / 256 x 256 tiles: 8192 x 4096 x 4096 264 / 246 / 220,
+// 4096 x 4096 x 4096 129 / 123 / 112, 8192 x 768 x 3072 47 / 43 / 66, 8192 x 1024 x 4096 64 / 60 / 87, 4096 x 1024 x
+// 4096 42 / 48 / 80, 6000 x 2000 x 2000 70 / 72 / 62, 8192 x 1536 x 1536 47 / 53 / 48, 8192 x 2304 x 768 44 / 56 / 62.
+double large_tile_us(int bn, int bm, long tiles, const GemmArgs& a) {
+  const int nst = (a.K + 63) / 64;
+  const bool gelu = a.ep.act == ACT_GELU;
+  if (bn == 128) {
+    const long rem = tiles % 512;
+    const double last = rem == 0 ? 0 : rem <= 256 ? 0.66 : std::min(1.0, 0.66 + 0.34 * (rem - 256) / 128);
+    return (tiles / 512 + last) * (nst + (gelu ? 4.7 : 2.2)) * (a.K % 64 ? 1.15 : 1.0);
+  }
+  const long rounds = (tiles + 255) / 256;
+  return bm == 128 ? rounds * (0.9 * nst + (gelu ? 8 : 2)) : rounds * (1.65 * nst + (gelu ? 13 : 10));
+}
+
 TilePlan plan_tiles(const GemmArgs& a, const Split& sp) {
   auto tiles = [&](int bn, int bm) { return (long)((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   const int nst = (a.K + 63) / 64;
   if (a.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
-  if (nst >= 32 && tiles(256, 256) >= 512) return {256, 256, 2, 1};
   // (also where the small tiles' 32-bit epilogue offsets would not do)
-  if (tiles(128, 128) >= 196 || (size_t)a.M * a.N * 2 >= (1u << 31)) return {128, 128, 2, 1};
+  if (tiles(128, 128) >= 196 || (size_t)a.M * a.N * 2 >= (1u << 31)) {
+    const double us[3] = {large_tile_us(128, 128, tiles(128, 128), a), large_tile_us(256, 128, tiles(256, 128), a),
+                          large_tile_us(256, 256, tiles(256, 256), a)};
+    if (nst < 16 || (us[0] <= us[1] && us[0] <= us[2])) return {128, 128, 2, 1};
+    return us[1] <= us[2] ? TilePlan{256, 128, 3, 1} : TilePlan{256, 256, 2, 1};
+  }
   if (tiles(64, 64) >= 192) return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, 1};
   if (tiles(64, 32) >= 192) return {64, 32, 3, 1};
   if (tiles(32, 64) >= 192) return {32, 64, 3, 1};
@@ -329,7 +350,8 @@ template <int MODE>
 hipError_t pick_tiled(const GemmArgs& a, const Split& sp, hipStream_t s) {
   const TilePlan p = plan_tiles(a, sp);
   // waves n x m, ring, least waves per SIMD
-  if (p.bn == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
+  if (p.bn == 256 && p.bm == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
+  if (p.bn == 256) return launch_tiled<256, 128, 4, 2, 3, 1, MODE>(a, p.splits, sp, s);
   if (p.bn == 128) return launch_tiled<128, 128, 4, 2, 2, 4, MODE>(a, p.splits, sp, s);
   if (p.bn == 64 && p.bm == 64 && p.ring == 2) return launch_tiled<64, 64, 2, 2, 2, 4, MODE>(a, p.splits, sp, s);
   if (p.bn == 64 && p.bm == 64) return launch_tiled<64, 64, 2, 2, 4, 2, MODE>(a, p.splits, sp, s);

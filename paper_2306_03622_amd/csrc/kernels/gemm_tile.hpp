@@ -52,7 +52,10 @@ __device__ __forceinline__ void lds_wait_barrier() {
 // each wave waits until its own loads of the next stage have landed (all but the (NST - 2) LPS
 // youngest: loads return in order, and every wave issues LPS per stage) and its reads of this
 // stage have returned, so that behind the barrier the next stage is whole and this stage's slot
-// free, into which stage j + NST is then loaded. The barrier stands before the stage's last group of
+// free, into which stage j + NST is then loaded, by large tiles a few
+// loads per group of multiplications (8 waves' 8 loads at once queue for the load path, 16 cycles
+// each, and hold up the multiplications behind them: 8192 x 4096 x 4096, 236 -> 220 us; small tiles lose
+// by it). The barrier stands before the stage's last group of
 // multiplications, which therefore covers the first LDS reads of the next stage; within a stage
 // the fragments of a group are read one group ahead.
 //
@@ -75,8 +78,10 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
   constexpr int TA = BN / 8 / NW, TB = BM / 8 / NW, LPS = TA + TB;   // 1 KB loads per wave and stage
   constexpr int WN = BN / WGN, WM = BM / WGM, NB = WN / 16, MB = WM / 16;
   constexpr bool PAIR = NB % 2 == 0;
-  constexpr int IG = NB >= 8 ? 4 : PAIR ? 2 : 1;       // weight fragments per group
+  constexpr int IG = PAIR ? 2 : 1;       // weight fragments per group
   constexpr int GP = NB / IG, T = 2 * GP;              // groups per 32-deep half stage, per stage
+  constexpr int SP = LPS <= 4 ? 1 : NST > 2 ? T : T / 2;   // groups over which a stage's loads are spread
+  constexpr int PER = (LPS + SP - 1) / SP;             // loads per group
   constexpr int RUN = PAIR ? 8 : 4, NR = NB * 4 / RUN; // outputs per run, runs per lane and row block
   constexpr bool EPF = VEC && NR * MB <= 4;
   static_assert(BN % (8 * NW) == 0 && BM % (8 * NW) == 0 && WN % 16 == 0 && WM % 16 == 0 && NB % IG == 0 &&
@@ -159,30 +164,35 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
     kh = tap / a.KW;
     kw = tap - kh * a.KW;
   }
-  auto issue = [&](int slot) __attribute__((always_inline)) {
+  // loads [lo, hi) of this wave's LPS loads of the next stage, into ring slot `slot`
+  auto issue = [&](int slot, int lo, int hi) __attribute__((always_inline)) {
     const uint32_t dst = lds0 + slot * SBYTES;
     const bool edge = sl >= full;                 // the ragged last stage
 #pragma unroll
-    for (int t = 0; t < TA; ++t)
-      lds_load16(rw, dst + (wave * TA + t) * 1024, (ta[t] & edge) ? kOffNone : offa[t], sl * (PK ? 2048 : 128));
-    if constexpr (MODE == X_ROWS) {
-#pragma unroll
-      for (int t = 0; t < TB; ++t)
-        lds_load16(rx, dst + ABYTES + (wave * TB + t) * 1024, (tb & edge) ? kOffNone : offb[t], sl * 128);
-    } else {
-      const uint32_t toff = (uint32_t)(((kh * a.W + kw) * a.C + c0) * 2);
-#pragma unroll
-      for (int t = 0; t < TB; ++t) {
-        const bool ok = ((unsigned)(ih0[t] + kh) < (unsigned)a.H) & ((unsigned)(iw0[t] + kw) < (unsigned)a.W);
-        lds_load16(rx, dst + ABYTES + (wave * TB + t) * 1024, ok ? offb[t] + toff : kOffNone, 0);
+    for (int u = 0; u < LPS; ++u) {
+      if (u < lo || u >= hi) continue;
+      if (u < TA) {
+        lds_load16(rw, dst + (wave * TA + u) * 1024, (ta[u] & edge) ? kOffNone : offa[u], sl * (PK ? 2048 : 128));
+      } else {
+        const int t = u - TA;
+        const uint32_t d = dst + ABYTES + (wave * TB + t) * 1024;
+        if constexpr (MODE == X_ROWS) {
+          lds_load16(rx, d, (tb & edge) ? kOffNone : offb[t], sl * 128);
+        } else {
+          const bool ok = ((unsigned)(ih0[t] + kh) < (unsigned)a.H) & ((unsigned)(iw0[t] + kw) < (unsigned)a.W);
+          lds_load16(rx, d, ok ? offb[t] + (uint32_t)(((kh * a.W + kw) * a.C + c0) * 2) : kOffNone, 0);
+        }
       }
+    }
+    if (hi < LPS) return;
+    ++sl;
+    if constexpr (MODE == X_CONV64) {
       c0 += 64;
       if (c0 == a.C) {
         c0 = 0;
         if (++kw == a.KW) { kw = 0; ++kh; }
       }
     }
-    ++sl;
   };
 
   f32x4 acc[NB][MB];
@@ -260,31 +270,34 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
 
 #pragma unroll
   for (int i = 0; i < NST; ++i)
-    if (i < n) issue(i);
+    if (i < n) issue(i, 0, LPS);
   if (n >= NST) lds_wait_barrier<(NST - 1) * LPS>();
   else lds_wait_barrier<0>();
   const char* cur = lds;
-  int slot = 0, j = 0;
+  int slot = 0, j = 0, pend = -1;               // pend: the slot whose stage is not all issued yet
   read(cur, 0);
   // WAIT: loads of stages beyond the next that may be in flight; MORE: a next stage exists;
   // ISSUE: so does stage j + NST
-#define TP_STAGE(WAIT, MORE, ISSUE)                             \
-  {                                                             \
-    const int ns = slot + 1 == NST ? 0 : slot + 1;              \
-    const char* nxt = lds + ns * SBYTES;                        \
-    _Pragma("unroll") for (int t = 0; t < T; ++t) {             \
-      if (MORE && t == T - 1) {                                 \
-        lds_wait_barrier<(WAIT)>();                             \
-        if (ISSUE) issue(slot);                                 \
-      }                                                         \
-      if (t + 1 < T) read(cur, t + 1);                          \
-      else if (MORE) read(nxt, 0);                              \
-      multiply(t);                                              \
-      __builtin_amdgcn_sched_barrier(0);                        \
-    }                                                           \
-    cur = nxt;                                                  \
-    slot = ns;                                                  \
-    ++j;                                                        \
+#define TP_STAGE(WAIT, MORE, ISSUE)                                             \
+  {                                                                             \
+    const int ns = slot + 1 == NST ? 0 : slot + 1;                              \
+    const char* nxt = lds + ns * SBYTES;                                        \
+    _Pragma("unroll") for (int t = 0; t < T; ++t) {                             \
+      if (MORE && t == T - 1) {                                                 \
+        lds_wait_barrier<(WAIT)>();                                             \
+        if (ISSUE) issue(slot, 0, PER);                                         \
+      } else if ((t + 1) * PER < LPS && pend >= 0) {                            \
+        issue(pend, (t + 1) * PER, (t + 2) * PER < LPS ? (t + 2) * PER : LPS);  \
+      }                                                                         \
+      if (t + 1 < T) read(cur, t + 1);                                          \
+      else if (MORE) read(nxt, 0);                                              \
+      multiply(t);                                                              \
+      __builtin_amdgcn_sched_barrier(0);                                        \
+    }                                                                           \
+    pend = ISSUE && PER < LPS ? slot : -1;                                      \
+    cur = nxt;                                                                  \
+    slot = ns;                                                                  \
+    ++j;                                                                        \
   }
   while (j + NST < n) TP_STAGE((NST - 2) * LPS, true, true)
   // the last stages, R more after each

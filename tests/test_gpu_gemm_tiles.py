@@ -29,8 +29,10 @@ SHAPES = [
     (1152, 1900, "64 x 64, two stages, blocked weights"),
     (1224, 2570, "128 x 128, ragged"),
     (1280, 2570, "128 x 128, blocked weights"),
-    (2056, 14850, "256 x 256, ragged"),
-    (2048, 16300, "256 x 256, blocked weights"),
+    (1032, 8010, "256 x 128, ragged"),
+    (2048, 4000, "256 x 128, blocked weights"),
+    (4088, 4000, "256 x 256, ragged"),
+    (4096, 4090, "256 x 256, blocked weights"),
 ]
 
 
