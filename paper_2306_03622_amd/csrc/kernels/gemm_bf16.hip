@@ -283,22 +283,29 @@ hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) 
 
 // Tile shape (output features x rows), ring depth and k split of a tiled contraction, by how many
 // tiles a shape gives the 256 CUs. Measured on MI355X over every contraction of ResNet-50 and
-// BERT-base at batch 1, 8 and 32 and MLP layers of 64 to 8192 rows, under graph replay with
-// 32 x 32 to 256 x 256 tiles (us; tiles in brackets):
-//   128 x 128, two per CU, from 196 tiles: 25088 x 128 x 1152 [196] 14.1 against 15.0 with
-//     64 x 64, 1568 x 2048 x 512 [208] 8.4 against 9.3; below, 1024 x 3072 x 768 [192] 11.6
-//     against 10.3, 6272 x 256 x 2304 [98] 19.9 against 15.4.
+// BERT-base at batch 1, 8 and 32 and MLP layers of 64 to 8192 rows, under graph replay, weights and
+// inputs rotating so that they come from beyond the L2s (us; tiles in brackets):
+//   128 x 128, two per CU, from 196 tiles and for more than 64 features: 25088 x 128 x 1152 [196] 14.2
+//     against 15.9 with 64 x 64, 1568 x 2048 x 512 [208] 8.9 against 10.0; below, 1024 x 3072 x 768 [192]
+//     11.8 against 11.4, 6272 x 256 x 2304 [98] 22 against 16; 100352 x 64 x 576 [784] 23 against 17. Up to
+//     one tile per CU with three stages in the ring (100352 / 4 x 128 x 512 [196] 8.9, with two 9.8).
 //     From 16 stages on, 256 x 256 or 256 x 128 instead where large_tile_us says so.
 //   64 x 64 from 192 tiles, with four stages in the ring while two per CU hold all tiles
-//     (1024 x 768 x 3072 [192] 12.7, with two stages 23; 256 x 4096 x 4096 [256] 16.1 against 31), else
-//     with two stages and up to five per CU (100352 x 64 x 64 [1568] 7.7 against 9.8 with four).
-//   64 x 32, then 32 x 64, from 192 tiles, else 32 x 32.
-// A k split costs a reduction, a launch of 2 to 3 us, so only contractions of 36 stages and more
-// whose tiles leave CUs idle are split, each split keeping 9 stages: 64 x 32 tiles from 64 of
-// them, up to 448 workgroups (392 x 512 x 4608 [104, 4 splits] 11.5, unsplit 32 x 32 14.7), else
-// 32 x 32, up to 256 (49 x 512 x 4608 [32, 8 splits] 7.8, unsplit 16; 196 x 256 x 2304 [56, 4
-// splits] 6.9, unsplit 7.6). Not a contraction with a row LayerNorm: 128 x 768 x 3072 [96] 7.1
-// unsplit, 7.5 split.
+//     (1024 x 768 x 3072 [192] 12.9, with two stages 23; 256 x 4096 x 4096 [256] 16.8 against 31), else
+//     with two stages and up to five per CU (100352 x 64 x 64 [1568] 7.7 against 10.5 with four).
+//     3 x 3 convolutions of 64 stages and more on at most one such tile per CU are split in two
+//     (1568 x 512 x 4608 [200] 20.5, unsplit 24).
+//   64 x 32 from 176 tiles, two per CU with five stages (480 x 768 x 3072 [180] 10.4 against 10.9 with
+//     32 x 32, 1568 x 256 x 1024 [196] 5.3 against 6.1 with three stages).
+//   Else 32 x 32, with six stages in the ring where that is at most one tile per CU (196 x 512 x 1024
+//     [112] 4.3, with four 4.6) and the contraction deep enough to fill it, else with four (128 x 3072 x
+//     768 [384] 5.1 against 5.4).
+// A k split costs a reduction, a launch of 2 to 3 us, so otherwise only contractions of 36 stages and
+// more whose tiles leave CUs idle are split, each split keeping 9 stages: 64 x 32 tiles from 64 of
+// them, up to 448 workgroups (392 x 512 x 4608 [104, 4 splits] 12.3, unsplit 32 x 32 14.7), else
+// 32 x 32, up to 256 (49 x 512 x 4608 [32, 8 splits] 7.3, unsplit 16; 196 x 256 x 2304 [56, 4
+// splits] 6.9, unsplit 7.6). Not a contraction with a row LayerNorm: 128 x 768 x 3072 [96] 8.0
+// unsplit, 8.6 split.
 struct TilePlan {
   int bn, bm, ring, splits;
 };
@@ -322,43 +329,47 @@ double large_tile_us(int bn, int bm, long tiles, const GemmArgs& a) {
   return bm == 128 ? rounds * (0.9 * nst + (gelu ? 8 : 2)) : rounds * (1.65 * nst + (gelu ? 13 : 10));
 }
 
-TilePlan plan_tiles(const GemmArgs& a, const Split& sp) {
+TilePlan plan_tiles(const GemmArgs& a, const Split& sp, bool conv) {
   auto tiles = [&](int bn, int bm) { return (long)((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   const int nst = (a.K + 63) / 64;
   if (a.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
   // (also where the small tiles' 32-bit epilogue offsets would not do)
-  if (tiles(128, 128) >= 196 || (size_t)a.M * a.N * 2 >= (1u << 31)) {
+  if ((tiles(128, 128) >= 196 && a.N > 64) || (size_t)a.M * a.N * 2 >= (1u << 31)) {
     const double us[3] = {large_tile_us(128, 128, tiles(128, 128), a), large_tile_us(256, 128, tiles(256, 128), a),
                           large_tile_us(256, 256, tiles(256, 256), a)};
-    if (nst < 16 || (us[0] <= us[1] && us[0] <= us[2])) return {128, 128, 2, 1};
+    if (nst < 16 || (us[0] <= us[1] && us[0] <= us[2])) return {128, 128, tiles(128, 128) <= 256 ? 3 : 2, 1};
     return us[1] <= us[2] ? TilePlan{256, 128, 3, 1} : TilePlan{256, 256, 2, 1};
   }
-  if (tiles(64, 64) >= 192) return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, 1};
-  if (tiles(64, 32) >= 192) return {64, 32, 3, 1};
-  if (tiles(32, 64) >= 192) return {32, 64, 3, 1};
-  if (sp.partials && nst >= 36 && !a.ep.ln_g) {
+  const size_t per_split = (size_t)a.M * a.N * 4;
+  const long most = sp.partials ? (long)(sp.partial_bytes / per_split) : 1;    // splits that fit the scratch
+  if (tiles(64, 64) >= 192) {
+    const bool deep_conv = conv && nst >= 64 && tiles(64, 64) <= 256 && most >= 2;
+    return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, deep_conv ? 2 : 1};
+  }
+  if (tiles(64, 32) >= 176) return {64, 32, 5, 1};
+  if (nst >= 36 && !a.ep.ln_g) {
     const bool wide = tiles(64, 32) >= 64;
     const long nt = wide ? tiles(64, 32) : tiles(32, 32);
-    const size_t per_split = (size_t)a.M * a.N * 4;
-    const int z = (int)std::min<long>({(wide ? 448 : 256) / nt, nst / 9, (long)(sp.partial_bytes / per_split)});
-    if (z > 1) return wide ? TilePlan{64, 32, 3, z} : TilePlan{32, 32, 4, z};
+    const int z = (int)std::min<long>({(wide ? 448 : 256) / nt, nst / 9, most});
+    if (z > 1) return wide ? TilePlan{64, 32, 5, z} : TilePlan{32, 32, 6, z};
   }
-  return {32, 32, 4, 1};
+  return {32, 32, tiles(32, 32) <= 256 && nst >= 8 ? 6 : 4, 1};
 }
 
 template <int MODE>
 hipError_t pick_tiled(const GemmArgs& a, const Split& sp, hipStream_t s) {
-  const TilePlan p = plan_tiles(a, sp);
+  const TilePlan p = plan_tiles(a, sp, MODE == X_CONV64);
   // waves n x m, ring, least waves per SIMD
   if (p.bn == 256 && p.bm == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
   if (p.bn == 256) return launch_tiled<256, 128, 4, 2, 3, 1, MODE>(a, p.splits, sp, s);
-  if (p.bn == 128) return launch_tiled<128, 128, 4, 2, 2, 4, MODE>(a, p.splits, sp, s);
-  if (p.bn == 64 && p.bm == 64 && p.ring == 2) return launch_tiled<64, 64, 2, 2, 2, 4, MODE>(a, p.splits, sp, s);
-  if (p.bn == 64 && p.bm == 64) return launch_tiled<64, 64, 2, 2, 4, 2, MODE>(a, p.splits, sp, s);
-  if (p.bn == 64) return launch_tiled<64, 32, 2, 2, 3, 4, MODE>(a, p.splits, sp, s);
-  if (p.bm == 64) return launch_tiled<32, 64, 1, 4, 3, 4, MODE>(a, p.splits, sp, s);
+  if (p.bn == 128 && p.ring == 2) return launch_tiled<128, 128, 4, 2, 2, 4, MODE>(a, p.splits, sp, s);
+  if (p.bn == 128) return launch_tiled<128, 128, 4, 2, 3, 2, MODE>(a, p.splits, sp, s);
+  if (p.bm == 64 && p.ring == 2) return launch_tiled<64, 64, 2, 2, 2, 4, MODE>(a, p.splits, sp, s);
+  if (p.bm == 64) return launch_tiled<64, 64, 2, 2, 4, 2, MODE>(a, p.splits, sp, s);
+  if (p.bn == 64) return launch_tiled<64, 32, 2, 2, 5, 2, MODE>(a, p.splits, sp, s);
   if (a.N % 8) return launch_tiled<32, 32, 2, 2, 4, 4, MODE, false>(a, p.splits, sp, s);
-  return launch_tiled<32, 32, 2, 2, 4, 4, MODE>(a, p.splits, sp, s);
+  if (p.ring == 4) return launch_tiled<32, 32, 2, 2, 4, 4, MODE>(a, p.splits, sp, s);
+  return launch_tiled<32, 32, 2, 2, 6, 3, MODE>(a, p.splits, sp, s);
 }
 
 bool ep_ok(const Epilogue& ep) {

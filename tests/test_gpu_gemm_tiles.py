@@ -15,20 +15,22 @@ SHAPES = [
     (64, 33, "32 x 32, one stage"),
     (72, 35, "32 x 32, ragged stage of 8"),
     (200, 65, "32 x 32, ragged"),
-    (512, 40, "32 x 32, blocked weights"),
-    (1000, 131, "32 x 32, ragged rows"),
-    (1000, 700, "64 x 32, ragged"),
-    (1024, 390, "64 x 32, blocked weights"),
-    (3080, 70, "32 x 64, ragged"),
-    (3200, 90, "32 x 64, blocked weights"),
+    (512, 40, "32 x 32, six stages, blocked weights"),
+    (1000, 131, "32 x 32, six stages, ragged"),
+    (1152, 240, "32 x 32, four stages, blocked weights"),
+    (1000, 700, "64 x 32, five stages, ragged"),
+    (1024, 390, "64 x 32, five stages, blocked weights"),
     (2400, 40, "64 x 32 split over k, ragged"),
     (2560, 50, "64 x 32 split over k, blocked weights"),
+    (64, 20000, "64 x 64, four stages, few features"),
     (776, 1000, "64 x 64, four stages, ragged"),
     (1024, 800, "64 x 64, four stages, blocked weights"),
     (776, 2600, "64 x 64, two stages, ragged"),
     (1152, 1900, "64 x 64, two stages, blocked weights"),
-    (1224, 2570, "128 x 128, ragged"),
-    (1280, 2570, "128 x 128, blocked weights"),
+    (1224, 2570, "128 x 128, three stages, ragged"),
+    (1280, 2570, "128 x 128, three stages, blocked weights"),
+    (520, 8010, "128 x 128, two stages, ragged"),
+    (512, 8510, "128 x 128, two stages, blocked weights"),
     (1032, 8010, "256 x 128, ragged"),
     (2048, 4000, "256 x 128, blocked weights"),
     (4088, 4000, "256 x 256, ragged"),
