@@ -16,15 +16,16 @@ namespace tp {
 namespace k {
 namespace {
 
-// FULL: S == SMAX, so every key tile is valid at compile time (with a run-time tile count
-// the conditional MFMA accumulators compiled to hundreds of register copies)
-template <int SMAX, bool FULL, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restrict__ qkv, int S_arg, int H,
+// The sequence length is a template argument, so every key tile is known at compile time (with a
+// run-time tile count the conditional MFMA accumulators compiled to hundreds of register copies:
+// S 96, 5 samples of 12 heads, 4.8 us against 4.0 us for S 128).
+template <int S, int NW>
+__global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restrict__ qkv, int H,
                                                        uint16_t* __restrict__ out) {
-  constexpr int LDK = 72, LDV = 80, NT = SMAX / 16, NTHR = 64 * NW;
-  const int S = FULL ? SMAX : S_arg;
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[SMAX * LDK];
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[SMAX * LDV];
+  constexpr int LDK = 72, LDV = 80, NT = S / 16, NTHR = 64 * NW;
+  static_assert(S % 32 == 0, "whole 32-key blocks");
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[S * LDK];
+  __shared__ __attribute__((aligned(16))) uint16_t Vs[S * LDV];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, g = lane >> 4;
   const int h = blockIdx.y, b = blockIdx.z;
@@ -46,8 +47,7 @@ __global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restric
   // took 5.6 / 5.5 us per launch at BERT-base batch 1 / 8 with the best padding of several;
   // other transposes, by lanes holding 64 consecutive keys or by an 8 x 8 exchange among
   // lanes, 6.7-7.4 us; all the same bits.)
-  constexpr int NV = SMAX * 8 / NTHR;
-  static_assert(SMAX * 8 % NTHR == 0 && SMAX % 64 == 0, "staging map");
+  constexpr int NV = (S * 8 + NTHR - 1) / NTHR;
   uint4 kv[NV], vv[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
@@ -67,39 +67,33 @@ __global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restric
   __syncthreads();
 
   if (!active) return;
-  const int nt = S >> 4;
-
   f32x4 sc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (t < nt) {
-      const uint16_t* krow = &Ks[(16 * t + r) * LDK + (g << 3)];
-      sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(krow)),
-                                                      as_bf16x8(qf0), sc[t], 0, 0, 0);
-      sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(krow + 32)),
-                                                      as_bf16x8(qf1), sc[t], 0, 0, 0);
-    }
+    const uint16_t* krow = &Ks[(16 * t + r) * LDK + (g << 3)];
+    sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(krow)),
+                                                    as_bf16x8(qf0), sc[t], 0, 0, 0);
+    sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*reinterpret_cast<const uint4*>(krow + 32)),
+                                                    as_bf16x8(qf1), sc[t], 0, 0, 0);
   }
   float mx = -INFINITY;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    if (t < nt)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[t][e]);
+    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[t][e]);
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   float sum = 0.f;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    if (t < nt)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // exp((s - max) / sqrt(64)) as one hardware base-2 exponential
-        const float p = __builtin_amdgcn_exp2f((sc[t][e] - mx) * (0.125f * 1.44269504088896341f));
-        sc[t][e] = p;
-        sum += p;
-      }
+    for (int e = 0; e < 4; ++e) {
+      // exp((s - max) / sqrt(64)) as one hardware base-2 exponential
+      const float p = __builtin_amdgcn_exp2f((sc[t][e] - mx) * (0.125f * 1.44269504088896341f));
+      sc[t][e] = p;
+      sum += p;
+    }
   sum += __shfl_xor(sum, 16, 64);
   sum += __shfl_xor(sum, 32, 64);
   const float inv = 1.f / sum;
@@ -109,51 +103,62 @@ __global__ __launch_bounds__(64 * NW) void k_attention(const uint16_t* __restric
   for (int dt = 0; dt < 4; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < NT / 2; ++u) {
-    if (2 * u < nt) {
-      const f32x4 p0 = sc[2 * u], p1 = sc[2 * u + 1];
-      uint4 pa;
-      pa.x = f2bf2(p0[0] * inv, p0[1] * inv);
-      pa.y = f2bf2(p0[2] * inv, p0[3] * inv);
-      pa.z = f2bf2(p1[0] * inv, p1[1] * inv);
-      pa.w = f2bf2(p1[2] * inv, p1[3] * inv);
+    const f32x4 p0 = sc[2 * u], p1 = sc[2 * u + 1];
+    uint4 pa;
+    pa.x = f2bf2(p0[0], p0[1]);
+    pa.y = f2bf2(p0[2], p0[3]);
+    pa.z = f2bf2(p1[0], p1[1]);
+    pa.w = f2bf2(p1[2], p1[3]);
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        // V^T fragment of keys 32 u + 4 g + 0..3 (lo) and 16 further (hi), dim 16 dt + r, read
-        // transposed from row-major V: within a 16-lane group, lane l receives element l % 4 of
-        // the 8-byte pieces the group's lanes l / 4 + 4 j (j = 0..3) address, so lane s of the
-        // group addresses key row (s % 16) / 4 at dims 16 dt + 4 (s % 4)
-        const uint16_t* vr = &Vs[(32 * u + 4 * g + (r >> 2)) * LDV + 16 * dt + 4 * (r & 3)];
-        typedef short v4s __attribute__((ext_vector_type(4)));
-        const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)vr);
-        const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(vr + 16 * LDV));
-        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(pa), as_bf16x8(make_uint4(l2.x, l2.y, h2.x, h2.y)),
-                                                        o[dt], 0, 0, 0);
-      }
+    for (int dt = 0; dt < 4; ++dt) {
+      // V^T fragment of keys 32 u + 4 g + 0..3 (lo) and 16 further (hi), dim 16 dt + r, read
+      // transposed from row-major V: within a 16-lane group, lane l receives element l % 4 of
+      // the 8-byte pieces the group's lanes l / 4 + 4 j (j = 0..3) address, so lane s of the
+      // group addresses key row (s % 16) / 4 at dims 16 dt + 4 (s % 4)
+      const uint16_t* vr = &Vs[(32 * u + 4 * g + (r >> 2)) * LDV + 16 * dt + 4 * (r & 3)];
+      typedef short v4s __attribute__((ext_vector_type(4)));
+      const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)vr);
+      const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(vr + 16 * LDV));
+      const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+      o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(pa), as_bf16x8(make_uint4(l2.x, l2.y, h2.x, h2.y)),
+                                                      o[dt], 0, 0, 0);
     }
   }
-  // lane holds O[query q0 + 4 g + e][d = 16 dt + r]
+  // lane holds O[query q0 + 4 g + e][d = 16 dt + r]; the query's 1 / sum is with lane 4 g + e
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int e = 0; e < 4; ++e) {
+    const float scale = __shfl(inv, 4 * g + e, 64);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      out[((size_t)b * S + q0 + 4 * g + e) * D + h * 64 + 16 * dt + r] = f2bf(o[dt][e]);
+    for (int dt = 0; dt < 4; ++dt)
+      out[((size_t)b * S + q0 + 4 * g + e) * D + h * 64 + 16 * dt + r] = f2bf(o[dt][e] * scale);
+  }
 }
 
 }  // namespace
 
 hipError_t attention(const uint16_t* qkv, int B, int S, int H, uint16_t* out, hipStream_t s) {
   if (!qkv || !out || B < 1 || H < 1 || S < 32 || (S & 31) || S > 256) return hipErrorInvalidValue;
-  // four waves (64 queries) per workgroup: with one or two, staging K and V once per
-  // workgroup costs more than the extra workgroups gain (BERT-base at batch 8: 0.790 ms warm
-  // with four, 0.839 with two, 0.915 with one; with the present staging, two waves at batch
-  // 1, where four leave 24 workgroups on 256 CUs: 0.462 -> 0.475 ms)
-  constexpr int NW = 4;
-  dim3 grid((S + 16 * NW - 1) / (16 * NW), H, B), block(64 * NW);
-  if (S == 128) (void)launch((k_attention<128, true, NW>), grid, block, 0, s, qkv, S, H, out);
-  else if (S < 128) (void)launch((k_attention<128, false, NW>), grid, block, 0, s, qkv, S, H, out);
-  else if (S == 256) (void)launch((k_attention<256, true, NW>), grid, block, 0, s, qkv, S, H, out);
-  else (void)launch((k_attention<256, false, NW>), grid, block, 0, s, qkv, S, H, out);
+  // Waves (16 queries each) per workgroup, each of which stages K and V once: up to 128 keys four
+  // (with one or two, staging costs more than the extra workgroups gain: BERT-base at batch 8, whole
+  // warm pass 0.790 ms with four, 0.839 with two, 0.915 with one). Longer sequences take four while
+  // that leaves CUs idle (S 256, 60 sample-heads: 5.1 us against 6.1 with eight), else eight, which fill
+  // a CU that the staged K and V leave room for two workgroups on (96 / 384 sample-heads: 6.5 / 19.0 us
+  // against 7.5 / 26.4), or from 192 sample-heads on a wave for every 16 queries of a sequence of up to
+  // 192, of which the second workgroup of eight would have few (S 160, 192 / 384: 6.5 / 9.9 us against 7.6 / 12.4).
+  const long heads = (long)H * B;
+  const int nw = S <= 128 || 2 * heads < 192 ? 4 : S <= 192 && heads >= 192 ? S / 16 : 8;
+  const dim3 grid((S + 16 * nw - 1) / (16 * nw), H, B), block(64 * nw);
+  auto go = [&](auto kern) { (void)launch(kern, grid, block, 0, s, qkv, H, out); };
+  switch (S) {
+    case 32: go(k_attention<32, 4>); break;
+    case 64: go(k_attention<64, 4>); break;
+    case 96: go(k_attention<96, 4>); break;
+    case 128: go(k_attention<128, 4>); break;
+    case 160: nw == 4 ? go(k_attention<160, 4>) : nw == 8 ? go(k_attention<160, 8>) : go(k_attention<160, 10>); break;
+    case 192: nw == 4 ? go(k_attention<192, 4>) : nw == 8 ? go(k_attention<192, 8>) : go(k_attention<192, 12>); break;
+    case 224: nw == 4 ? go(k_attention<224, 4>) : go(k_attention<224, 8>); break;
+    default: nw == 4 ? go(k_attention<256, 4>) : go(k_attention<256, 8>); break;
+  }
   return hipGetLastError();
 }
 
