@@ -95,8 +95,9 @@ hipError_t run_resnet(ExecCtx& x) {
                         c.c.stride, c.c.pad, ep, x.split, x.stream);
   };
 
-  TP_TRY(conv(0, static_cast<const uint16_t*>(x.in), buf[0], nullptr, k::ACT_RELU));
-  TP_TRY(k::maxpool3s2(buf[0], B, g[0].hout, g[0].hout, g[0].c.cout, buf[1], x.stream));
+  TP_TRY(x.wait->need(0));
+  TP_TRY(k::stem_pool(static_cast<const uint16_t*>(x.in), B, image, image, x.t<uint16_t>(0, TP_ROLE_W),
+                      x.t<uint16_t>(0, TP_ROLE_B), buf[1], x.stream));     // 7x7 convolution, ReLU, max-pool
   int cur = 1;
   uint32_t li = 1;
   const int blocks[4] = {3, 4, 6, 3};

@@ -8,14 +8,12 @@
 // register e of lane l holds D[n = 4 (l / 16) + e][m = l % 16]: four consecutive output
 // features of one row, which the epilogue stores as one vector.
 //
-// Kernels here (the skinny M <= 32 case is in gemv_bf16.hip):
+// Kernels here (the skinny M <= 32 case is in gemv_bf16.hip, the 3-channel stem in stem.hip):
 //   * k_gemm (gemm_tile.hpp): BN x BM output tiles over a ring of 64-deep k-stages in LDS that
 //     loads fill directly, and a deterministic split over k when a deep contraction's tiles
 //     cannot fill the chip. The activation loader is either a plain row-major matrix or an
 //     NHWC implicit-GEMM (im2col) gather for convolutions, k = (kh * KW + kw) * C + c, matching
 //     OHWI weight rows.
-//   * k_conv_smallc: convolutions with fewer than 8 input channels (the ResNet stem),
-//     whose input window rows are staged in LDS.
 #include <algorithm>
 
 #include "gemm_tile.hpp"
@@ -24,174 +22,6 @@ namespace tp {
 namespace k {
 
 namespace {
-
-// ------------------------------------------------------------------ few input channels
-
-// Convolutions whose input has at most 4 channels (the ResNet stem: 7 x 7, stride 2,
-// 3 channels), where an im2col row is not made of 16-byte runs. A workgroup owns all
-// (<= 64) output channels and SC_W consecutive output pixels of `rows` consecutive output
-// rows of one sample. Its loads are issued together before any LDS store, so it waits for
-// memory once: the weights as 16-byte loads of the flat [N][K] array (re-laid out in LDS
-// with rows zero-padded to a multiple of 32), and every input row the windows of its output
-// rows touch (zero outside the image). Wave w multiplies the 16 pixels 16w .. 16w+15 of each
-// output row against every output channel: the activation operand is gathered element by
-// element from the staged rows (k = (kh * KW + kw) * C + c, so a k-run inside one filter row
-// is a run of a staged input row), the weight operand read as 16-byte vectors.
-constexpr int SC_W = 64, SC_MAXC = 4, SC_MAXK = 7, SC_MAXS = 2, SC_MAXR = 8;
-constexpr int SC_KP = ((SC_MAXK * SC_MAXK * SC_MAXC + 31) / 32) * 32;   // 224
-constexpr int SC_KS = SC_KP + 8;                                        // weight row stride in LDS
-constexpr int SC_RL = ((SC_W - 1) * SC_MAXS + SC_MAXK) * SC_MAXC;       // longest staged input row
-constexpr int SC_MAXIN = (SC_MAXR - 1) * SC_MAXS + SC_MAXK;             // input rows of SC_MAXR output rows
-constexpr int SC_PER = (SC_RL + 255) / 256;                             // staged elements per thread and row
-constexpr int SC_WV = (64 * SC_MAXK * SC_MAXK * SC_MAXC * 2 / 16 + 255) / 256;  // 16-byte weight loads per thread
-// the staged input rows, or the flat weights (with the tail of their last 16-byte vector) on their way to wl
-constexpr int SC_RLV = (SC_MAXC * 2 + SC_RL + 7) / 8 * 8;   // staged row stride of the vector path (below)
-constexpr int SC_XL = SC_MAXIN * SC_RLV > 64 * SC_MAXK * SC_MAXK * SC_MAXC + 8 ? SC_MAXIN * SC_RLV
-                                                                             : 64 * SC_MAXK * SC_MAXK * SC_MAXC + 8;
-
-// IN: input rows staged at most (SC_MAXK for one output row per workgroup, SC_MAXIN for up to
-// SC_MAXR), so that a workgroup of one output row computes no addresses for rows it never loads.
-// VX: image rows of a multiple of 8 elements from a 16-byte aligned image are staged as whole
-// 16-byte vectors (the window's first element then sits `sh` elements into the staged row;
-// vectors outside the image read as zero, and the image's edges fall on vector boundaries), so
-// that staging costs a few vector loads per thread instead of element loads with their
-// addressing; otherwise element by element.
-template <int C, int IN, bool VX>
-__global__ __launch_bounds__(256) void k_conv_smallc(GemmArgs a, int rows) {
-  __shared__ __align__(16) uint16_t wl[64 * SC_KS];
-  __shared__ __align__(16) uint16_t xl[SC_XL];
-  __shared__ __align__(16) int koff[SC_KP];   // staged-row offset of window element k, -1 beyond K
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int KW = a.KW, K = a.K, KWC = KW * C, KH = K / KWC;
-  const int KP = (K + 31) & ~31;
-  const int ow0 = blockIdx.x * SC_W, b = blockIdx.z;
-  const int rl = ((SC_W - 1) * a.stride + KW) * C;
-  const int oh_first = blockIdx.y * rows;
-  const int nrows = min(rows, a.Ho - oh_first);          // >= 1: the grid covers Ho exactly
-  const int nin = (nrows - 1) * a.stride + KH;            // input rows staged
-  const int ih_first = oh_first * a.stride - a.pad, iw0 = ow0 * a.stride - a.pad;
-  // vector path: staged row r holds image-row elements from vector vfirst on, so the window's
-  // element j sits at sh + j; element path: at j
-  const int vfirst = (iw0 * C) >> 3;                      // floor division (iw0 may be negative)
-  const int sh = VX ? iw0 * C - vfirst * 8 : 0;
-  const int rs = VX ? (sh + rl + 7) & ~7 : rl;            // staged row stride
-  const int nvec = rs >> 3;
-  for (int k = tid; k < KP; k += 256) {
-    const int kh = k / KWC;
-    koff[k] = k < K ? kh * rs + (k - kh * KWC) : -1;
-  }
-  // every global load first: the flat weights, then the staged input rows
-  const int nw = a.N * K;                         // weight elements; the array starts 16-byte aligned
-  const int nv = (nw * 2 + 15) / 16;
-  uint4 wv[SC_WV];
-#pragma unroll
-  for (int u = 0; u < SC_WV; ++u) {
-    const int i = u * 256 + tid;
-    // the last vector may extend past the array end; it stays inside the 256-byte
-    // aligned allocation unit of the weight tensor
-    wv[u] = i < nv ? reinterpret_cast<const uint4*>(a.w)[i] : make_uint4(0, 0, 0, 0);
-  }
-  static_assert(IN <= SC_MAXIN, "staged rows");
-  static_assert(SC_RLV / 8 <= 128, "two vectors per lane cover a staged row");
-  constexpr int XE = VX ? 1 : IN, XU = VX ? 1 : SC_PER;       // element path: rows x elements per thread
-  constexpr int XR = VX ? (IN + 3) / 4 : 1;                   // vector path: rows per wave (row r = wave + 4 i)
-  uint16_t xv[XE][XU];
-  uint4 xq[XR][2];
-  if constexpr (VX) {
-    const int rowv = (a.W * C) >> 3;                        // vectors per image row
-#pragma unroll
-    for (int i = 0; i < XR; ++i) {
-      const int r = wave + 4 * i, ih = ih_first + r;
-      const bool hin = r < nin && ih >= 0 && ih < a.H;
-      const uint4* xrow = reinterpret_cast<const uint4*>(a.x + ((size_t)b * a.H + (hin ? ih : 0)) * a.W * C);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int vi = lane + 64 * h, gv = vfirst + vi;
-        xq[i][h] = (hin && vi < nvec && gv >= 0 && gv < rowv) ? xrow[gv] : make_uint4(0, 0, 0, 0);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < IN; ++r) {
-      const int ih = ih_first + r;
-      const bool hin = r < nin && ih >= 0 && ih < a.H;
-      const uint16_t* xrow = a.x + ((size_t)b * a.H + (hin ? ih : 0)) * a.W * C;
-#pragma unroll
-      for (int u = 0; u < SC_PER; ++u) {
-        const int j = u * 256 + tid;
-        const int col = j / C, iw = iw0 + col;
-        xv[r][u] = (hin && j < rl && iw >= 0 && iw < a.W) ? xrow[(size_t)iw * C + (j - col * C)] : (uint16_t)0;
-      }
-    }
-  }
-  // the flat weights through xl, then padded rows into wl (four threads per row, every fourth
-  // k: no division by the run-time row length), then the input rows into xl
-#pragma unroll
-  for (int u = 0; u < SC_WV; ++u) {
-    const int i = u * 256 + tid;
-    if (i < nv) reinterpret_cast<uint4*>(xl)[i] = wv[u];
-  }
-  __syncthreads();
-  const int wn = tid >> 2;
-  for (int k = tid & 3; k < KP; k += 4)
-    wl[wn * SC_KS + k] = (wn < a.N && k < K) ? xl[wn * K + k] : (uint16_t)0;
-  __syncthreads();
-  if constexpr (VX) {
-#pragma unroll
-    for (int i = 0; i < XR; ++i) {
-      const int r = wave + 4 * i;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int vi = lane + 64 * h;
-        if (r < nin && vi < nvec) *reinterpret_cast<uint4*>(&xl[r * rs + vi * 8]) = xq[i][h];
-      }
-    }
-  } else {
-#pragma unroll
-    for (int r = 0; r < IN; ++r)
-#pragma unroll
-      for (int u = 0; u < SC_PER; ++u) {
-        const int j = u * 256 + tid;
-        if (r < nin && j < rl) xl[r * rs + j] = xv[r][u];
-      }
-  }
-  __syncthreads();
-
-  const int p = wave * 16 + (lane & 15), q = lane >> 4;
-  const int pofs = p * a.stride * C;
-  for (int r = 0; r < nrows; ++r) {
-    const int oh = oh_first + r, rbase = r * a.stride * rs + pofs + sh;
-    f32x4 acc[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the same number of k-steps in every lane; element reads are unconditional (offset
-    // clamped to 0) and masked afterwards
-    for (int ks = 0; ks < KP / 32; ++ks) {
-      const int k0 = ks * 32 + q * 8;
-      const int4 o0 = *reinterpret_cast<const int4*>(&koff[k0]);
-      const int4 o1 = *reinterpret_cast<const int4*>(&koff[k0 + 4]);
-      const int o[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
-      uint32_t bw[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t v = xl[(o[e] < 0 ? 0 : o[e]) + rbase];
-        bw[e >> 1] |= (o[e] < 0 ? 0u : v) << (16 * (e & 1));
-      }
-      const uint4 bv = make_uint4(bw[0], bw[1], bw[2], bw[3]);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint4 av = *reinterpret_cast<const uint4*>(&wl[(16 * g + (lane & 15)) * SC_KS + k0]);
-        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(av), as_bf16x8(bv), acc[g], 0, 0, 0);
-      }
-    }
-    if (ow0 + p < a.Wo) {
-      const int m = ((b * a.Ho) + oh) * a.Wo + ow0 + p;
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        if (16 * g < a.N) store_row4(a, m, 16 * g + 4 * q, acc[g]);
-    }
-  }
-}
 
 // y = epilogue(sum over splits z = 0, 1, ... of P[z]) for four consecutive outputs per thread.
 // A thread fetches the epilogue's inputs and ZG partials before it adds any (a launch that
@@ -411,26 +241,6 @@ hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16
   a.ep.w_packed = 0;
   if ((size_t)B * H * W * C * 2 >= (1u << 31) || (size_t)O * KH * KW * C * 2 >= (1u << 31))
     return hipErrorInvalidValue;   // the tiled kernel addresses x and w through 32-bit buffer offsets
-  if (C <= SC_MAXC && KH <= SC_MAXK && KW <= SC_MAXK && stride <= SC_MAXS && O <= 64 && (O & 15) == 0 &&
-      a.K <= SC_KP) {
-    // enough workgroups to fill the chip, each reusing its staged weights over `rows` rows
-    const int segs = (Wo + SC_W - 1) / SC_W;
-    const int rows = max(1, min(SC_MAXR, segs * Ho * B / 448));
-    dim3 grid(segs, (Ho + rows - 1) / rows, B);
-    auto go = [&](auto kern) { (void)launch(kern, grid, dim3(256), 0, s, a, rows); };
-    const bool one = rows == 1, vx = (W * C) % 8 == 0 && ((uintptr_t)x & 15) == 0;
-    // the vector path for the channel counts of network stems (RGB, RGBA), the element path
-    // otherwise
-    if (vx && C == 3) one ? go(k_conv_smallc<3, SC_MAXK, true>) : go(k_conv_smallc<3, SC_MAXIN, true>);
-    else if (vx && C == 4) one ? go(k_conv_smallc<4, SC_MAXK, true>) : go(k_conv_smallc<4, SC_MAXIN, true>);
-    else switch (C) {
-      case 1: one ? go(k_conv_smallc<1, SC_MAXK, false>) : go(k_conv_smallc<1, SC_MAXIN, false>); break;
-      case 2: one ? go(k_conv_smallc<2, SC_MAXK, false>) : go(k_conv_smallc<2, SC_MAXIN, false>); break;
-      case 3: one ? go(k_conv_smallc<3, SC_MAXK, false>) : go(k_conv_smallc<3, SC_MAXIN, false>); break;
-      default: one ? go(k_conv_smallc<4, SC_MAXK, false>) : go(k_conv_smallc<4, SC_MAXIN, false>); break;
-    }
-    return hipGetLastError();
-  }
   if ((C & 63) == 0) return pick_tiled<X_CONV64>(a, sp, s);
   return hipErrorInvalidValue;
 }

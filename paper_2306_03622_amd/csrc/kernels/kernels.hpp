@@ -61,12 +61,15 @@ hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N
 
 // Implicit-GEMM convolution: x NHWC [B][H][W][C] bf16, w OHWI [O][KH][KW][C] bf16,
 // y NHWC [B][Ho][Wo][O] via the epilogue (M = B*Ho*Wo rows of N = O). C % 64 == 0 (implicit
-// GEMM), or C <= 4 with O <= 64, O % 16 == 0 and a filter of at most 7 x 7, stride <= 2 (the
-// small-channel kernel of a network's stem); other channel counts return
-// hipErrorInvalidValue. x and w each below 2 GiB; a 1x1 stride-1 convolution is a linear
-// layer and has its size limits too.
+// GEMM; other channel counts return hipErrorInvalidValue; a network's 3-channel stem has stem_pool). x and
+// w each below 2 GiB; a 1x1 stride-1 convolution is a linear layer and has its size limits too.
 hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
                      int stride, int pad, const Epilogue& ep, const Split& sp, hipStream_t s);
+
+// The ResNet stem: 7 x 7 stride-2 pad-3 convolution of NHWC x [B][H][W][3] to 64 channels (w OHWI,
+// bias may be null) rounded to bf16, ReLU, then 3x3 stride-2 pad-1 max-pool, y NHWC [B][Hp][Wp][64].
+hipError_t stem_pool(const uint16_t* x, int B, int H, int W, const uint16_t* w, const uint16_t* bias, uint16_t* y,
+                     hipStream_t s);
 
 // fp32 linear: y[M][N] = act(x[M][K] * w[N][K]^T + bias). K % 4 == 0.
 hipError_t linear_f32(const float* x, int M, int K, const float* w, int N, const float* bias, int act, float* y,
@@ -86,9 +89,6 @@ hipError_t embed_ln(const int32_t* ids, int M, int S, int D, int vocab, const ui
 // Multi-head self-attention, head dim 64, no mask: qkv bf16 [B*S][3*H*64] (Q|K|V blocks,
 // heads contiguous inside each) -> out bf16 [B*S][H*64]. S % 32 == 0, S <= 256.
 hipError_t attention(const uint16_t* qkv, int B, int S, int H, uint16_t* out, hipStream_t s);
-
-// 3x3 stride-2 pad-1 max-pool, NHWC bf16; C % 8 == 0.
-hipError_t maxpool3s2(const uint16_t* x, int B, int H, int W, int C, uint16_t* y, hipStream_t s);
 
 // Mean over HW positions: x [B][HW][C] -> y [B][C], bf16.
 hipError_t avgpool(const uint16_t* x, int B, int HW, int C, uint16_t* y, hipStream_t s);

@@ -1,4 +1,4 @@
-// Pooling (NHWC bf16), the host-to-device gather copy, the cache touch and the bounded delay
+// Average pooling (NHWC bf16), the host-to-device gather copy, the cache touch and the bounded delay
 // kernel.
 #include <algorithm>
 
@@ -9,59 +9,6 @@
 namespace tp {
 namespace k {
 namespace {
-
-// One thread per (sample, output pixel, 8 channels). The nine taps are loaded together (a tap
-// in the padding reads the nearest pixel inside the image and is then ignored, so every load
-// is in bounds and none waits for another) and reduced in the fixed order dh, dw; padded taps
-// never win, as if skipped. (With each tap's load behind its bounds test the loads were issued
-// one after another: 7.0 us per launch at ResNet-50 batch 1.)
-__global__ __launch_bounds__(256) void k_maxpool3s2(const uint16_t* __restrict__ x, int B, int H, int W, int C,
-                                                    int Ho, int Wo, uint16_t* __restrict__ y) {
-  const int c8n = C >> 3;
-  const long total = (long)B * Ho * Wo * c8n;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int c8 = (int)(i % c8n);
-  long p = i / c8n;
-  const int ow = (int)(p % Wo);
-  p /= Wo;
-  const int oh = (int)(p % Ho);
-  const int b = (int)(p / Ho);
-  uint4 v[9];
-  bool ok[9];
-#pragma unroll
-  for (int dh = 0; dh < 3; ++dh) {
-    const int ih = oh * 2 - 1 + dh;
-    const bool hin = ih >= 0 && ih < H;
-    const int ihc = ih < 0 ? 0 : (ih >= H ? H - 1 : ih);
-#pragma unroll
-    for (int dw = 0; dw < 3; ++dw) {
-      const int iw = ow * 2 - 1 + dw;
-      const int iwc = iw < 0 ? 0 : (iw >= W ? W - 1 : iw);
-      ok[dh * 3 + dw] = hin && iw >= 0 && iw < W;
-      v[dh * 3 + dw] = *reinterpret_cast<const uint4*>(x + (((size_t)b * H + ihc) * W + iwc) * C + c8 * 8);
-    }
-  }
-  float m[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) m[e] = -INFINITY;
-#pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    if (!ok[t]) continue;
-    const uint32_t w[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      m[2 * e] = fmaxf(m[2 * e], bf2f(w[e] & 0xffff));
-      m[2 * e + 1] = fmaxf(m[2 * e + 1], bf2f(w[e] >> 16));
-    }
-  }
-  uint4 o;
-  o.x = f2bf2(m[0], m[1]);
-  o.y = f2bf2(m[2], m[3]);
-  o.z = f2bf2(m[4], m[5]);
-  o.w = f2bf2(m[6], m[7]);
-  *reinterpret_cast<uint4*>(y + (((size_t)b * Ho + oh) * Wo + ow) * C + c8 * 8) = o;
-}
 
 // one thread per (sample, channel), positions summed in order in fp32
 // One thread per (sample, channel). The HW loads are independent, so they are issued 8 at
@@ -141,14 +88,6 @@ __global__ void k_delay(int iters) {
 }
 
 }  // namespace
-
-hipError_t maxpool3s2(const uint16_t* x, int B, int H, int W, int C, uint16_t* y, hipStream_t s) {
-  if (!x || !y || B < 1 || H < 1 || W < 1 || C < 8 || (C & 7)) return hipErrorInvalidValue;
-  const int Ho = (H + 2 - 3) / 2 + 1, Wo = (W + 2 - 3) / 2 + 1;
-  const long total = (long)B * Ho * Wo * (C >> 3);
-  (void)launch(k_maxpool3s2, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, x, B, H, W, C, Ho, Wo, y);
-  return hipGetLastError();
-}
 
 hipError_t avgpool(const uint16_t* x, int B, int HW, int C, uint16_t* y, hipStream_t s) {
   if (!x || !y || B < 1 || HW < 1 || C < 1) return hipErrorInvalidValue;
