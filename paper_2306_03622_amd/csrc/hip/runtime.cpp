@@ -70,7 +70,6 @@ void destroy_streams(tp_ctx* c) {
   if (c->touch_sink) (void)hipFree(c->touch_sink);
   if (c->copy[1]) (void)hipStreamDestroy(c->copy[1]);
   if (c->capture) (void)hipStreamDestroy(c->capture);
-  if (c->req_done) (void)hipEventDestroy(c->req_done);
   for (auto* v : {&c->tl.copy_begin, &c->tl.copy_end, &c->tl.exec_begin})
     for (hipEvent_t e : *v)
       if (e) (void)hipEventDestroy(e);
@@ -469,7 +468,7 @@ hipError_t settle(Model* m, hipStream_t stream) {
 }
 
 tp_status begin_request(tp_ctx* c, hipStream_t stream) {
-  if (c->any_request && stream != c->last_stream) TP_HIP(hipStreamWaitEvent(stream, c->req_done, 0));
+  if (c->req_done && stream != c->last_stream) TP_HIP(hipStreamWaitEvent(stream, c->req_done, 0));
   return ok();
 }
 
@@ -481,9 +480,8 @@ tp_status end_request(tp_ctx* c, Model* m, hipStream_t stream) {
   }
   TP_HIP(hipEventRecord(m->last_use, stream));
   m->used = true;
-  TP_HIP(hipEventRecord(c->req_done, stream));
+  c->req_done = m->last_use;
   c->last_stream = stream;
-  c->any_request = true;
   return ok();
 }
 
@@ -765,7 +763,6 @@ tp_status tp_create(const tp_config* cfg, tp_ctx** out) {
   // which then reports it)
   if (e == hipSuccess && scratch_init(c->device) != hipSuccess) (void)hipGetLastError();
 
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->req_done, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->claim_ev, hipEventDisableTiming);
   if (e == hipSuccess && (cfg->flags & TP_FLAG_TRACE)) e = hipEventCreate(&c->tl.start);
@@ -782,7 +779,6 @@ tp_status tp_destroy(tp_ctx* c) {
   if (!c) return fail(TP_E_INVAL, "NULL context");
   hipError_t e = sync_copies(c);
   if (e == hipSuccess && c->exec) e = hipStreamSynchronize(c->exec);
-  if (e == hipSuccess && c->any_request) e = hipEventSynchronize(c->req_done);
   for (auto& kv : c->models) {
     if (kv.second->used) (void)hipEventSynchronize(kv.second->last_use);
     free_model(kv.second.get());
@@ -884,6 +880,7 @@ tp_status tp_unregister_model(tp_ctx* c, int32_t id) {
   // the copy streams may still read the host copy; the last use may still read the extent
   TP_HIP(sync_copies(c));
   if (m->used) TP_HIP(hipEventSynchronize(m->last_use));
+  if (c->req_done == m->last_use) c->req_done = nullptr;   // complete, and every earlier request with it
   if (c->policy->resident(id)) c->policy->evict(id);
   c->retired.erase(std::remove_if(c->retired.begin(), c->retired.end(),
                                   [&](const tp_ctx::Retired& r) { return r.model == id; }),

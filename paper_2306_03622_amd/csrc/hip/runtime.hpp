@@ -159,9 +159,9 @@ struct tp_ctx {
   std::unordered_map<int32_t, std::unique_ptr<tp::Model>> models;
   int32_t next_id = 1;
   // request ordering across caller streams
+  // completion of the last request: the last-use event of the model it served (null: none outstanding)
   hipEvent_t req_done = nullptr;
   hipStream_t last_stream = nullptr;
-  bool any_request = false;
   std::vector<hipEvent_t> trace_ev;            // completion ring of tp_run_trace
   uint64_t admit_calls = 0, admit_ns_total = 0, admit_ns_max = 0;   // admissions that missed
   uint64_t last_admit_ns = 0;                                         // the latest of them

@@ -218,12 +218,11 @@ def _check(L, status):
 
 def _ptr(x):
     """Device or host address of a torch tensor, an int or None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
-    if hasattr(x, "data_ptr"):
-        return x.data_ptr()
+    data_ptr = getattr(x, "data_ptr", None)
+    if data_ptr is not None:
+        return data_ptr()
     if hasattr(x, "cuda_stream"):
         return x.cuda_stream
     raise TypeError(type(x))
@@ -298,7 +297,10 @@ def tp_unregister_model(ctx, model_id):
 
 
 def tp_infer(ctx, model_id, input_dev, batch, output_dev, stream=None):
-    _check(lib(), lib().tp_infer(ctx, model_id, _ptr(input_dev), batch, _ptr(output_dev), _ptr(stream)))
+    L = _lib or lib()
+    status = L.tp_infer(ctx, model_id, _ptr(input_dev), batch, _ptr(output_dev), _ptr(stream))
+    if status != TP_OK:
+        _check(L, status)
 
 
 def tp_infer_noalloc(ctx, model_id, input_dev, batch, output_dev, stream=None):
