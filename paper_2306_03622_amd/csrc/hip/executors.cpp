@@ -108,11 +108,24 @@ hipError_t run_resnet(ExecCtx& x) {
       for (int i = 0; i < 5; ++i)
         if (i != cur) o[n++] = i;
       const bool proj = b == 0;
-      TP_TRY(conv(li, buf[cur], buf[o[0]], nullptr, k::ACT_RELU));          // 1x1
+      // the block's 1x1 and projection read the same input: one launch, when no weights are on their way
+      bool paired = false;
+      if (proj && !x.wait->swapping) {
+        const ConvGeom &c0 = g[li], &c1 = g[li + 3];
+        k::Epilogue e0, e1;
+        e0.bias = x.t<uint16_t>(li, TP_ROLE_B);
+        e0.act = k::ACT_RELU;
+        e0.out = buf[o[0]];
+        e1.bias = x.t<uint16_t>(li + 3, TP_ROLE_B);
+        e1.out = buf[o[2]];
+        TP_TRY(k::conv1x1_pair(buf[cur], B, c0.hin, c0.hin, c0.c.cin, x.t<uint16_t>(li, TP_ROLE_W), c0.c.cout, e0,
+                               x.t<uint16_t>(li + 3, TP_ROLE_W), c1.c.cout, c1.c.stride, e1, &paired, x.stream));
+      }
+      if (!paired) TP_TRY(conv(li, buf[cur], buf[o[0]], nullptr, k::ACT_RELU));   // 1x1
       TP_TRY(conv(li + 1, buf[o[0]], buf[o[1]], nullptr, k::ACT_RELU));     // 3x3, stage stride
       const uint16_t* res = buf[cur];
       if (proj) {                                                           // projection shortcut
-        TP_TRY(conv(li + 3, buf[cur], buf[o[2]], nullptr, k::ACT_NONE));
+        if (!paired) TP_TRY(conv(li + 3, buf[cur], buf[o[2]], nullptr, k::ACT_NONE));
         res = buf[o[2]];
       }
       TP_TRY(conv(li + 2, buf[o[1]], buf[o[3]], res, k::ACT_RELU));         // 1x1 + shortcut, ReLU

@@ -225,15 +225,23 @@ hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N
   return pick_tiled<X_ROWS>(a, sp, s);
 }
 
-hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
-                     int stride, int pad, const Epilogue& ep, const Split& sp, hipStream_t s) {
+namespace {
+
+// Two contractions share a launch up to this many 32 x 32 tiles: a launch is then mostly its fixed part (some
+// 4 us: the launch, the first operands' round trip, the drain and the epilogue), which the pair pays once. Beyond,
+// larger tiles in launches of their own win. ResNet-50 at 224 x 224, four pairs, warm us per pass with limits of
+// 0 / 512 / 1024 / 2048 / 4096 tiles: batch 1 (240 to 980 tiles) 267 / 262 / 257 / 258 / 259, 2 (480 to 1960) 298 / 298 /
+// 296 / 297 / 298, 4 (960 to 3900) 348 / 348 / 347 / 350 / 356, 8 403 / 405 / 402 / 408 / 409.
+constexpr long kPairTiles = 1024;
+
+// Checks a convolution and fills its argument block (also a 1x1 stride-1 one's, as a linear layer's).
+hipError_t conv_args(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
+                     int stride, int pad, const Epilogue& ep, GemmArgs* out) {
   if (!x || !w || B < 1 || H < 1 || W < 1 || C < 1 || O < 1 || KH < 1 || KW < 1 || stride < 1 || pad < 0 ||
       !ep_ok(ep) || ep.ln_g)
     return hipErrorInvalidValue;
   const int Ho = (H + 2 * pad - KH) / stride + 1, Wo = (W + 2 * pad - KW) / stride + 1;
   if (Ho < 1 || Wo < 1) return hipErrorInvalidValue;
-  if (KH == 1 && KW == 1 && stride == 1 && pad == 0 && (C & 7) == 0)
-    return linear_bf16(x, B * H * W, C, w, O, ep, sp, s);
   GemmArgs a{};
   a.x = x; a.w = w; a.M = B * Ho * Wo; a.N = O; a.K = KH * KW * C;
   a.H = H; a.W = W; a.C = C; a.KW = KW; a.stride = stride; a.pad = pad; a.Ho = Ho; a.Wo = Wo;
@@ -241,8 +249,39 @@ hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16
   a.ep.w_packed = 0;
   if ((size_t)B * H * W * C * 2 >= (1u << 31) || (size_t)O * KH * KW * C * 2 >= (1u << 31))
     return hipErrorInvalidValue;   // the tiled kernel addresses x and w through 32-bit buffer offsets
-  if ((C & 63) == 0) return pick_tiled<X_CONV64>(a, sp, s);
-  return hipErrorInvalidValue;
+  if (C & 63) return hipErrorInvalidValue;
+  *out = a;
+  return hipSuccess;
+}
+
+}  // namespace
+
+hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
+                     int stride, int pad, const Epilogue& ep, const Split& sp, hipStream_t s) {
+  if (KH == 1 && KW == 1 && stride == 1 && pad == 0 && (C & 7) == 0 && !ep.ln_g)
+    return linear_bf16(x, B * H * W, C, w, O, ep, sp, s);
+  GemmArgs a{};
+  const hipError_t e = conv_args(x, B, H, W, C, w, O, KH, KW, stride, pad, ep, &a);
+  return e == hipSuccess ? pick_tiled<X_CONV64>(a, sp, s) : e;
+}
+
+hipError_t conv1x1_pair(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w0, int O0, const Epilogue& ep0,
+                        const uint16_t* w1, int O1, int stride1, const Epilogue& ep1, bool* done, hipStream_t s) {
+  *done = false;
+  GemmArgs a{}, b{};
+  hipError_t e = conv_args(x, B, H, W, C, w0, O0, 1, 1, 1, 0, ep0, &a);
+  if (e == hipSuccess) e = conv_args(x, B, H, W, C, w1, O1, 1, 1, stride1, 0, ep1, &b);
+  if (e != hipSuccess) return e;
+  const int tna = (a.N + 31) / 32, tma = (a.M + 31) / 32, tnb = (b.N + 31) / 32, tmb = (b.M + 31) / 32;
+  const long tiles = (long)tna * tma + (long)tnb * tmb;
+  // rows past the skinny kernel's, and neither contraction long enough for the plan to split it
+  if (tiles > kPairTiles || a.M <= 32 || b.M <= 32 || C >= 36 * 64 || a.N % 8 || b.N % 8) return hipSuccess;
+  a.splits = b.splits = 1;
+  a.kst = b.kst = (C + 63) / 64;
+  *done = true;
+  if (stride1 == 1) (void)launch(k_gemm_pair<X_ROWS>, dim3((unsigned)tiles), dim3(256), 0, s, a, tna, tma, b, tnb, tmb);
+  else (void)launch(k_gemm_pair<X_CONV64>, dim3((unsigned)tiles), dim3(256), 0, s, a, tna, tma, b, tnb, tmb);
+  return hipGetLastError();
 }
 
 }  // namespace k

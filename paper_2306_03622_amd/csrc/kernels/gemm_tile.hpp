@@ -72,8 +72,11 @@ __device__ __forceinline__ void lds_wait_barrier() {
 // EPF: the epilogue's bias and residual are loaded before the first operands, so that their
 // round trip overlaps the main loop (small tiles; large ones have no registers to spare).
 // VEC: N is a multiple of 8 (4 for a single block per wave), runs of outputs are whole vectors.
-template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, int MINW, bool VEC>
-__global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int tn, int tm) {
+// The body of workgroup `id` of `total`; lds: gemm_lds bytes.
+constexpr size_t gemm_lds(int bn, int bm, int nst) { return (size_t)nst * (bn + bm) * 128; }
+
+template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, bool VEC>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int id, int total, char* lds) {
   constexpr int NW = WGN * WGM;
   constexpr int TA = BN / 8 / NW, TB = BM / 8 / NW, LPS = TA + TB;   // 1 KB loads per wave and stage
   constexpr int WN = BN / WGN, WM = BM / WGM, NB = WN / 16, MB = WM / 16;
@@ -87,7 +90,6 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
   static_assert(BN % (8 * NW) == 0 && BM % (8 * NW) == 0 && WN % 16 == 0 && WM % 16 == 0 && NB % IG == 0 &&
                     NST >= 2 && NST <= 8 && (VEC || !PAIR), "tile shape");
   constexpr int ABYTES = BN * 128, SBYTES = (BN + BM) * 128;
-  __shared__ __attribute__((aligned(1024))) char lds[NST * SBYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -98,9 +100,8 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
   // XCD x takes the x-th contiguous eighth of the tiles, which are ordered in bands of kBand
   // tile rows, so the tiles an XCD works on at a time share their operands' rows.
   constexpr int kBand = 8;
-  int id = blockIdx.x;
   {
-    const int total = gridDim.x, per = total >> 3, rem = total & 7, xcd = id & 7;
+    const int per = total >> 3, rem = total & 7, xcd = id & 7;
     id = xcd * per + min(xcd, rem) + (id >> 3);
   }
   const int z = a.splits > 1 ? id / (tn * tm) : 0;
@@ -350,6 +351,22 @@ __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int t
       }
     }
   }
+}
+
+template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, int MINW, bool VEC>
+__global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int tn, int tm) {
+  __shared__ __attribute__((aligned(1024))) char lds[gemm_lds(BN, BM, NST)];
+  gemm_tile<BN, BM, WGN, WGM, NST, MODE, PK, VEC>(a, tn, tm, blockIdx.x, gridDim.x, lds);
+}
+
+// Two independent contractions in one launch, 32 x 32 tiles: workgroups [0, na) the first, the others the
+// second. The same sums in the same order as in launches of their own with any tile (unsplit), so the same bits. Its rule: conv1x1_pair.
+template <int MODE_B>
+__global__ __launch_bounds__(256, 3) void k_gemm_pair(GemmArgs a, int tna, int tma, GemmArgs b, int tnb, int tmb) {
+  __shared__ __attribute__((aligned(1024))) char lds[gemm_lds(32, 32, 6)];
+  const int na = tna * tma;
+  if ((int)blockIdx.x < na) gemm_tile<32, 32, 2, 2, 6, X_ROWS, false, true>(a, tna, tma, blockIdx.x, na, lds);
+  else gemm_tile<32, 32, 2, 2, 6, MODE_B, false, true>(b, tnb, tmb, blockIdx.x - na, gridDim.x - na, lds);
 }
 
 }  // namespace k

@@ -66,6 +66,11 @@ hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N
 hipError_t conv_bf16(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w, int O, int KH, int KW,
                      int stride, int pad, const Epilogue& ep, const Split& sp, hipStream_t s);
 
+// Two 1x1 convolutions of the same input, the first of stride 1, in one launch where that is the faster
+// way (*done; else nothing is launched). The same bits as two conv_bf16 calls.
+hipError_t conv1x1_pair(const uint16_t* x, int B, int H, int W, int C, const uint16_t* w0, int O0, const Epilogue& ep0,
+                        const uint16_t* w1, int O1, int stride1, const Epilogue& ep1, bool* done, hipStream_t s);
+
 // The ResNet stem: 7 x 7 stride-2 pad-3 convolution of NHWC x [B][H][W][3] to 64 channels (w OHWI,
 // bias may be null) rounded to bf16, ReLU, then 3x3 stride-2 pad-1 max-pool, y NHWC [B][Hp][Wp][64].
 hipError_t stem_pool(const uint16_t* x, int B, int H, int W, const uint16_t* w, const uint16_t* bias, uint16_t* y,
