@@ -163,8 +163,9 @@ TilePlan plan_tiles(const GemmArgs& a, const Split& sp, bool conv) {
   auto tiles = [&](int bn, int bm) { return (long)((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   const int nst = (a.K + 63) / 64;
   if (a.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
-  // (also where the small tiles' 32-bit epilogue offsets would not do)
-  if ((tiles(128, 128) >= 196 && a.N > 64) || (size_t)a.M * a.N * 2 >= (1u << 31)) {
+  // beyond the 32-bit offsets of the epilogue that tiles of four blocks per wave fetch ahead
+  if ((size_t)a.M * a.N * 2 >= (1u << 31)) return {256, 128, 3, 1};
+  if (tiles(128, 128) >= 196 && a.N > 64) {
     const double us[3] = {large_tile_us(128, 128, tiles(128, 128), a), large_tile_us(256, 128, tiles(256, 128), a),
                           large_tile_us(256, 256, tiles(256, 256), a)};
     if (nst < 16 || (us[0] <= us[1] && us[0] <= us[2])) return {128, 128, tiles(128, 128) <= 256 ? 3 : 2, 1};
