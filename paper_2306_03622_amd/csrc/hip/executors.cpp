@@ -24,6 +24,13 @@ hipError_t run_mlp(ExecCtx& x) {
   const uint64_t bytes = round_up((uint64_t)B * W * (f32 ? 4 : 2), 256);
   char* buf[2] = {x.work, x.work + bytes};
   const void* cur = x.in;
+  if (!f32 && B > k::kSkinnyRows && ((uintptr_t)x.in & 15)) {
+    // the tiled contraction reads its input from 16-byte boundaries only: an input elsewhere is copied
+    // into the second buffer, which layer 0 does not write
+    TP_TRY(k::copy_aligned(static_cast<const uint16_t*>(x.in), (uint64_t)B * W, reinterpret_cast<uint16_t*>(buf[1]),
+                           x.stream));
+    cur = buf[1];
+  }
   for (int l = 0; l < L; ++l) {
     TP_TRY(x.wait->need(l));
     const bool last = l == L - 1;

@@ -216,13 +216,15 @@ hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N
   if (ep.w_packed && ((N & 15) || (K & 127))) return hipErrorInvalidValue;
   GemmArgs a{};
   a.x = x; a.w = w; a.M = M; a.N = N; a.K = K; a.ep = ep;
-  if (M <= 32) {
+  if (M <= kSkinnyRows) {
     a.splits = 1;
     hipError_t e = launch_skinny(a, s);
     return e == hipSuccess ? finish(a, s) : e;
   }
-  // the tiled kernel addresses x and w through 32-bit buffer offsets
-  if ((size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31)) return hipErrorInvalidValue;
+  // the tiled kernel addresses x and w through 32-bit buffer offsets, and loads them straight into LDS
+  // in 16-byte pieces, from 16-byte boundaries only
+  if ((size_t)M * K * 2 >= (1u << 31) || (size_t)N * K * 2 >= (1u << 31) || ((uintptr_t)x & 15) || ((uintptr_t)w & 15))
+    return hipErrorInvalidValue;
   return pick_tiled<X_ROWS>(a, sp, s);
 }
 
@@ -248,8 +250,9 @@ hipError_t conv_args(const uint16_t* x, int B, int H, int W, int C, const uint16
   a.H = H; a.W = W; a.C = C; a.KW = KW; a.stride = stride; a.pad = pad; a.Ho = Ho; a.Wo = Wo;
   a.ep = ep;
   a.ep.w_packed = 0;
-  if ((size_t)B * H * W * C * 2 >= (1u << 31) || (size_t)O * KH * KW * C * 2 >= (1u << 31))
-    return hipErrorInvalidValue;   // the tiled kernel addresses x and w through 32-bit buffer offsets
+  if ((size_t)B * H * W * C * 2 >= (1u << 31) || (size_t)O * KH * KW * C * 2 >= (1u << 31) || ((uintptr_t)x & 15) ||
+      ((uintptr_t)w & 15))
+    return hipErrorInvalidValue;   // the tiled kernel's 32-bit buffer offsets and 16-byte loads, as above
   if (C & 63) return hipErrorInvalidValue;
   *out = a;
   return hipSuccess;
@@ -276,7 +279,7 @@ hipError_t conv1x1_pair(const uint16_t* x, int B, int H, int W, int C, const uin
   const int tna = (a.N + 31) / 32, tma = (a.M + 31) / 32, tnb = (b.N + 31) / 32, tmb = (b.M + 31) / 32;
   const long tiles = (long)tna * tma + (long)tnb * tmb;
   // rows past the skinny kernel's, and neither contraction long enough for the plan to split it
-  if (tiles > kPairTiles || a.M <= 32 || b.M <= 32 || C >= 36 * 64 || a.N % 8 || b.N % 8) return hipSuccess;
+  if (tiles > kPairTiles || a.M <= kSkinnyRows || b.M <= kSkinnyRows || C >= 36 * 64 || a.N % 8 || b.N % 8) return hipSuccess;
   a.splits = b.splits = 1;
   a.kst = b.kst = (C + 63) / 64;
   *done = true;

@@ -54,8 +54,11 @@ struct Split {
   size_t partial_bytes = 0;
 };
 
+// Rows up to which a linear layer takes the skinny kernel.
+constexpr int kSkinnyRows = 32;
+
 // y[M][N] = x[M][K] * w[N][K]^T with the epilogue; bf16 in, fp32 accumulate. K % 8 == 0;
-// for M > 32, x and w each below 2 GiB (M K 2 and N K 2 bytes < 2^31).
+// for M > kSkinnyRows, x and w each below 2 GiB (M K 2 and N K 2 bytes < 2^31) and 16-byte aligned.
 hipError_t linear_bf16(const uint16_t* x, int M, int K, const uint16_t* w, int N, const Epilogue& ep,
                        const Split& sp, hipStream_t s);
 
@@ -94,6 +97,9 @@ hipError_t embed_ln(const int32_t* ids, int M, int S, int D, int vocab, const ui
 // Multi-head self-attention, head dim 64, no mask: qkv bf16 [B*S][3*H*64] (Q|K|V blocks,
 // heads contiguous inside each) -> out bf16 [B*S][H*64]. S % 32 == 0, S <= 256.
 hipError_t attention(const uint16_t* qkv, int B, int S, int H, uint16_t* out, hipStream_t s);
+
+// dst = src, n bf16 values (n % 8 == 0): dst 16-byte aligned, src at any element.
+hipError_t copy_aligned(const uint16_t* src, uint64_t n, uint16_t* dst, hipStream_t s);
 
 // Mean over HW positions: x [B][HW][C] -> y [B][C], bf16.
 hipError_t avgpool(const uint16_t* x, int B, int HW, int C, uint16_t* y, hipStream_t s);

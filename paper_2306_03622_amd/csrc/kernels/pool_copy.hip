@@ -1,5 +1,5 @@
-// Average pooling (NHWC bf16), the host-to-device gather copy, the cache touch and the bounded delay
-// kernel.
+// Average pooling (NHWC bf16), the host-to-device gather copy, the copy of an unaligned input, the
+// cache touch and the bounded delay kernel.
 #include <algorithm>
 
 #include "common.hpp"
@@ -50,6 +50,19 @@ __global__ __launch_bounds__(256) void k_gather(const uint4* __restrict__ src, u
   for (; i < n; i += stride) dst[i] = src[i];
 }
 
+// Eight bf16 values per thread, loaded one by one (the source starts at any element), stored as one
+// vector.
+__global__ __launch_bounds__(256) void k_copy_aligned(const uint16_t* __restrict__ src, uint4* __restrict__ dst,
+                                                      uint64_t n8) {
+  const uint64_t stride = (uint64_t)gridDim.x * 256;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
+    uint32_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = src[8 * i + e];
+    dst[i] = make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16);
+  }
+}
+
 // Loads in flight per thread, workgroups per touch (one per CU). Measured on MI355X, warm
 // ResNet-50 / BERT-base requests at batch 1 after a cache flush, with every warm request
 // touching: 397 / 534 us untouched; 376 / 528 with 32 workgroups, 373 / 508 with 64, 371 / 498
@@ -92,6 +105,13 @@ __global__ void k_delay(int iters) {
 hipError_t avgpool(const uint16_t* x, int B, int HW, int C, uint16_t* y, hipStream_t s) {
   if (!x || !y || B < 1 || HW < 1 || C < 1) return hipErrorInvalidValue;
   (void)launch(k_avgpool, dim3((B * C + 63) / 64), dim3(64), 0, s, x, B, HW, C, y);
+  return hipGetLastError();
+}
+
+hipError_t copy_aligned(const uint16_t* src, uint64_t n, uint16_t* dst, hipStream_t s) {
+  if (!src || !dst || n < 8 || (n & 7) || ((uintptr_t)dst & 15)) return hipErrorInvalidValue;
+  const uint64_t wgs = std::min<uint64_t>((n / 8 + 255) / 256, 4096);
+  (void)launch(k_copy_aligned, dim3((unsigned)wgs), dim3(256), 0, s, src, reinterpret_cast<uint4*>(dst), n / 8);
   return hipGetLastError();
 }
 
