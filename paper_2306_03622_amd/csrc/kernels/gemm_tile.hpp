@@ -35,7 +35,7 @@ __device__ __forceinline__ typename EpRun<R>::Raw ep_run_load(__amdgpu_buffer_rs
 // against 0.12 us). No register is written; the waits are lds_wait_barrier's.
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint32_t dst, uint32_t voff, int soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               ::"s"(dst), "v"(voff), "s"(r), "s"(soff));
+               ::"s"(dst), "v"(voff), "s"(r), "s"(soff) : "m0");
 }
 
 // Waits until at most N of this wave's vector-memory operations are in flight and its LDS reads
