@@ -117,7 +117,8 @@ __device__ __forceinline__ void linear_f32_tile(const float* __restrict__ x, int
   const int m = m0 + 16 * wave + r, n = n0 + 4 * q;
   if (m >= M) return;
   float* yr = y + (size_t)m * N + n;
-  if (n + 3 < N && (N & 3) == 0) {
+  // whole vectors where the caller's output starts at a 16-byte boundary (rows of N % 4 == 0 floats then all do)
+  if (n + 3 < N && (N & 3) == 0 && ((uintptr_t)y & 15) == 0) {
     const float4 bb = bias ? *reinterpret_cast<const float4*>(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
     *reinterpret_cast<float4*>(yr) = make_float4(act_apply(s[0][0] + bb.x, act), act_apply(s[0][1] + bb.y, act),
                                                  act_apply(s[0][2] + bb.z, act), act_apply(s[0][3] + bb.w, act));
