@@ -5,7 +5,7 @@ import pytest
 
 import synth
 from oracle import forward as oracle_forward
-from tests.common import infer, log, make_runtime
+from tests.common import infer, log, make_runtime, to_device, torch_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +41,30 @@ def test_rows_do_not_depend_on_each_other(batch):
     rt.close()
     assert np.array_equal(got[1:], clean[1:])
     assert np.all(np.isinf(got[0]))
+
+
+def test_more_rows_than_one_grid_dimension_holds():
+    # 64 rows per workgroup, 65536 workgroups in a grid dimension: the last rows take another, in a pass launched
+    # layer by layer and in a replayed graph whose buffers change
+    torch, dev = torch_dev()
+    width, batch = 8, 65536 * 64 + 70
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((batch, width), dtype=np.float32)
+    rows = np.r_[0:3, 65536 * 64 - 2:batch]
+    for layers in (1, 16):
+        log(f"fp32 {layers} x {width}, batch {batch}")
+        m = synth.mlp(layers, width, "f32", "none", seed=6)
+        rt, (mid,) = make_runtime([m], batch_max=batch)
+        ref = oracle_forward.forward(m, x[rows])
+        for _ in range(2):                       # the second pass has other buffers
+            err = oracle_forward.normwise_error(infer(rt, mid, m, x)[rows], ref).max()
+            log(f"  normwise error {err:.2e}")
+            assert err <= 1e-4
+        xd = to_device(x)
+        out = torch.full((batch, width), float("nan"), dtype=torch.float32, device=dev)
+        torch.cuda.synchronize()
+        s = torch.cuda.Stream(device=dev)
+        rt.infer(mid, xd, out, stream=s)
+        s.synchronize()
+        assert oracle_forward.normwise_error(out.cpu().numpy()[rows], ref).max() <= 1e-4
+        rt.close()
