@@ -292,8 +292,11 @@ std::vector<uint32_t> plan_cost(const std::vector<uint64_t>& unit_begin, uint64_
 
 namespace {
 
-// sustained rates of the layer kernels for the cost model (MI355X, bf16 MFMA kernels of
-// this library at the shapes of the model families; measured per kernel)
+// What a kernel of a swapping request takes in the cost model. These are not the warm times: a cold pass's
+// kernels are launched one by one, on weights that have just landed, while the copies go on. Constants
+// fitted to 516 warm passes (3.9 us, 800 TFLOP/s, 4 TB/s, within 14% rms) put the last chunks' boundaries too late:
+// cold us with these / 5 us, 400, 3.5 / the warm fit: ResNet-50 at 224 x 224, batch 1 991 / 1023 / 1104, 8 1022 / 1111 /
+// 1223, 32 1349 / 1456 / 1569; BERT-base at batch 8 3976 / 4030 / 4033; 12 x 1024 bf16 at batch 8 511 / 503 / 538.
 constexpr double kKernelUs = 7.0;            // launch, fill and drain of one dependent kernel
 constexpr double kFlopPerUs = 200.0e6;       // 200 TFLOP/s
 constexpr double kBytePerUs = 3.5e6;         // 3.5 TB/s
@@ -320,10 +323,11 @@ std::vector<double> layer_cost_us(const ModelSpec& m, int32_t batch) {
         t[l] = kernel_us(2 * B * hw_out * c.c.cout * k2 * c.c.cin,
                          2 * (c.c.cout * k2 * c.c.cin + B * hw_in * c.c.cin + B * hw_out * c.c.cout));
       }
-      // conv1 is followed by the max-pool; the FC by nothing but is preceded by the avg-pool
+      // conv1's kernel pools its output before it writes it; the FC is preceded by the avg-pool
       const ConvGeom& c0 = g[0];
-      const int hp = (c0.hout + 2 - 3) / 2 + 1;
-      t[0] += kernel_us(0, 2 * B * c0.c.cout * ((double)c0.hout * c0.hout + (double)hp * hp));
+      const double hp = (c0.hout + 2 - 3) / 2 + 1, k1 = (double)c0.c.k * c0.c.k * c0.c.cin;
+      t[0] = kernel_us(2 * B * c0.hout * c0.hout * c0.c.cout * k1,
+                       2 * (c0.c.cout * k1 + B * c0.hin * c0.hin * c0.c.cin + B * hp * hp * c0.c.cout));
       const double cls = m.dims[0];
       const ConvGeom& gl = g.back();
       t.back() = kernel_us(0, 2 * B * 2048 * ((double)gl.hout * gl.hout + 1)) +

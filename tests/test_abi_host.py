@@ -414,6 +414,18 @@ def test_cost_plan_of_workloads(cfg, batch):
     assert all(u > 0 for u in us)
 
 
+def test_cost_model_counts_the_kernels_of_a_layer():
+    # where the launches are all that counts (batch 1, 32 x 32 images) every ResNet-50 layer costs one kernel, the
+    # stem with its max-pool among them; the FC comes with the average pool; an encoder layer has seven
+    m = synth.resnet50(seed=1, image=32)
+    us = tp.tph_layer_costs(tp.ModelDesc.of(m), m.total_bytes, 1, L=tp.host_lib())
+    one = min(us)
+    assert max(us[:-1]) < 1.5 * one and 2 * one <= us[-1] < 2.5 * one
+    b = synth.bert(seed=1, layers=2, d=64, heads=1, ffn=64, seq=32, vocab=100, maxpos=32)
+    us = tp.tph_layer_costs(tp.ModelDesc.of(b), b.total_bytes, 1, L=tp.host_lib())
+    assert us[1] == us[2] and 6.5 * us[0] < us[1] < 7.5 * us[0]
+
+
 @settings(max_examples=200, deadline=None)
 @given(counts=st.lists(st.tuples(st.integers(0, 60), st.integers(0, 60)), min_size=1, max_size=12),
        alpha=st.sampled_from([0.0, 0.03125, 0.125, 0.25, 0.5, 0.75, 1.0]),
