@@ -17,6 +17,7 @@
 #include <algorithm>
 
 #include "gemm_tile.hpp"
+#include "tile_plan.hpp"
 
 namespace tp {
 namespace k {
@@ -111,85 +112,10 @@ hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) 
   return finish(a, s);
 }
 
-// Tile shape (output features x rows), ring depth and k split of a tiled contraction, by how many
-// tiles a shape gives the 256 CUs. Measured on MI355X over every contraction of ResNet-50 and
-// BERT-base at batch 1, 8 and 32 and MLP layers of 64 to 8192 rows, under graph replay, weights and
-// inputs rotating so that they come from beyond the L2s (us; tiles in brackets):
-//   128 x 128, two per CU, from 196 tiles and for more than 64 features: 25088 x 128 x 1152 [196] 14.2
-//     against 15.9 with 64 x 64, 1568 x 2048 x 512 [208] 8.9 against 10.0; below, 1024 x 3072 x 768 [192]
-//     11.8 against 11.4, 6272 x 256 x 2304 [98] 22 against 16; 100352 x 64 x 576 [784] 23 against 17. Up to
-//     one tile per CU with three stages in the ring (100352 / 4 x 128 x 512 [196] 8.9, with two 9.8).
-//     From 16 stages on, 256 x 256 or 256 x 128 instead where large_tile_us says so.
-//   64 x 64 from 192 tiles, with four stages in the ring while two per CU hold all tiles
-//     (1024 x 768 x 3072 [192] 12.9, with two stages 23; 256 x 4096 x 4096 [256] 16.8 against 31), else
-//     with two stages and up to five per CU (100352 x 64 x 64 [1568] 7.7 against 10.5 with four).
-//     3 x 3 convolutions of 64 stages and more on at most one such tile per CU are split in two
-//     (1568 x 512 x 4608 [200] 20.5, unsplit 24).
-//   64 x 32 from 176 tiles, two per CU with five stages (480 x 768 x 3072 [180] 10.4 against 10.9 with
-//     32 x 32, 1568 x 256 x 1024 [196] 5.3 against 6.1 with three stages).
-//   Else 32 x 32, with six stages in the ring where that is at most one tile per CU (196 x 512 x 1024
-//     [112] 4.3, with four 4.6) and the contraction deep enough to fill it, else with four (128 x 3072 x
-//     768 [384] 5.1 against 5.4).
-// A k split costs a reduction, a launch of 2 to 3 us, so otherwise only contractions of 36 stages and
-// more whose tiles leave CUs idle are split, each split keeping 9 stages: 64 x 32 tiles from 64 of
-// them, up to 448 workgroups (392 x 512 x 4608 [104, 4 splits] 12.3, unsplit 32 x 32 14.7), else
-// 32 x 32, up to 256 (49 x 512 x 4608 [32, 8 splits] 7.3, unsplit 16; 196 x 256 x 2304 [56, 4
-// splits] 6.9, unsplit 7.6). Not a contraction with a row LayerNorm: 128 x 768 x 3072 [96] 8.0
-// unsplit, 8.6 split.
-struct TilePlan {
-  int bn, bm, ring, splits;
-};
-
-// Time of a contraction with large tiles, a model fitted to the rates measured on MI355X. A round
-// of the chip (512 tiles of 128 x 128, two per CU, else 256) costs a rate per stage and a fixed
-// part, larger with a GELU; a last round of 128 x 128 tiles that leaves CUs with one tile costs
-// 0.66. Rows that are not whole 128-byte lines cost the smallest tiles, which load the most per
-// multiplication, 15%. Measured, us, with 128 x 128 / 256 x 128 / 256 x 256 tiles: 8192 x 4096 x 4096 264 / 246 / 220,
-// 4096 x 4096 x 4096 129 / 123 / 112, 8192 x 768 x 3072 47 / 43 / 66, 8192 x 1024 x 4096 64 / 60 / 87, 4096 x 1024 x
-// 4096 42 / 48 / 80, 6000 x 2000 x 2000 70 / 72 / 62, 8192 x 1536 x 1536 47 / 53 / 48, 8192 x 2304 x 768 44 / 56 / 62.
-double large_tile_us(int bn, int bm, long tiles, const GemmArgs& a) {
-  const int nst = (a.K + 63) / 64;
-  const bool gelu = a.ep.act == ACT_GELU;
-  if (bn == 128) {
-    const long rem = tiles % 512;
-    const double last = rem == 0 ? 0 : rem <= 256 ? 0.66 : std::min(1.0, 0.66 + 0.34 * (rem - 256) / 128);
-    return (tiles / 512 + last) * (nst + (gelu ? 4.7 : 2.2)) * (a.K % 64 ? 1.15 : 1.0);
-  }
-  const long rounds = (tiles + 255) / 256;
-  return bm == 128 ? rounds * (0.9 * nst + (gelu ? 8 : 2)) : rounds * (1.65 * nst + (gelu ? 13 : 10));
-}
-
-TilePlan plan_tiles(const GemmArgs& a, const Split& sp, bool conv) {
-  auto tiles = [&](int bn, int bm) { return (long)((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
-  const int nst = (a.K + 63) / 64;
-  if (a.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
-  // beyond the 32-bit offsets of the epilogue that tiles of four blocks per wave fetch ahead
-  if ((size_t)a.M * a.N * 2 >= (1u << 31)) return {256, 128, 3, 1};
-  if (tiles(128, 128) >= 196 && a.N > 64) {
-    const double us[3] = {large_tile_us(128, 128, tiles(128, 128), a), large_tile_us(256, 128, tiles(256, 128), a),
-                          large_tile_us(256, 256, tiles(256, 256), a)};
-    if (nst < 16 || (us[0] <= us[1] && us[0] <= us[2])) return {128, 128, tiles(128, 128) <= 256 ? 3 : 2, 1};
-    return us[1] <= us[2] ? TilePlan{256, 128, 3, 1} : TilePlan{256, 256, 2, 1};
-  }
-  const size_t per_split = (size_t)a.M * a.N * 4;
-  const long most = sp.partials ? (long)(sp.partial_bytes / per_split) : 1;    // splits that fit the scratch
-  if (tiles(64, 64) >= 192) {
-    const bool deep_conv = conv && nst >= 64 && tiles(64, 64) <= 256 && most >= 2;
-    return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, deep_conv ? 2 : 1};
-  }
-  if (tiles(64, 32) >= 176) return {64, 32, 5, 1};
-  if (nst >= 36 && !a.ep.ln_g) {
-    const bool wide = tiles(64, 32) >= 64;
-    const long nt = wide ? tiles(64, 32) : tiles(32, 32);
-    const int z = (int)std::min<long>({(wide ? 448 : 256) / nt, nst / 9, most});
-    if (z > 1) return wide ? TilePlan{64, 32, 5, z} : TilePlan{32, 32, 6, z};
-  }
-  return {32, 32, tiles(32, 32) <= 256 && nst >= 8 ? 6 : 4, 1};
-}
-
 template <int MODE>
 hipError_t pick_tiled(const GemmArgs& a, const Split& sp, hipStream_t s) {
-  const TilePlan p = plan_tiles(a, sp, MODE == X_CONV64);
+  const TileShape shape{a.M, a.N, a.K, MODE == X_CONV64, a.ep.act == ACT_GELU, a.ep.ln_g != nullptr};
+  const TilePlan p = plan_tiles(shape, sp.partials ? sp.partial_bytes : 0);
   // waves n x m, ring, least waves per SIMD
   if (p.bn == 256 && p.bm == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
   if (p.bn == 256) return launch_tiled<256, 128, 4, 2, 3, 1, MODE>(a, p.splits, sp, s);

@@ -10,35 +10,36 @@ from tests.common import infer, log, make_runtime
 
 pytestmark = pytest.mark.gpu
 
-# (width = features = k, batch, what the plan makes of it)
+# (width = features = k, batch, the plan: features and rows of a tile, k-stages in the ring, k splits); a width of a
+# multiple of 128 has blocked weights
 SHAPES = [
-    (64, 33, "32 x 32, one stage"),
-    (72, 35, "32 x 32, ragged stage of 8"),
-    (200, 65, "32 x 32, ragged"),
-    (512, 40, "32 x 32, six stages, blocked weights"),
-    (1000, 131, "32 x 32, six stages, ragged"),
-    (1152, 240, "32 x 32, four stages, blocked weights"),
-    (1000, 700, "64 x 32, five stages, ragged"),
-    (1024, 390, "64 x 32, five stages, blocked weights"),
-    (2400, 40, "64 x 32 split over k, ragged"),
-    (2560, 50, "64 x 32 split over k, blocked weights"),
-    (64, 20000, "64 x 64, four stages, few features"),
-    (776, 1000, "64 x 64, four stages, ragged"),
-    (1024, 800, "64 x 64, four stages, blocked weights"),
-    (776, 2600, "64 x 64, two stages, ragged"),
-    (1152, 1900, "64 x 64, two stages, blocked weights"),
-    (1224, 2570, "128 x 128, three stages, ragged"),
-    (1280, 2570, "128 x 128, three stages, blocked weights"),
-    (520, 8010, "128 x 128, two stages, ragged"),
-    (512, 8510, "128 x 128, two stages, blocked weights"),
-    (1032, 8010, "256 x 128, ragged"),
-    (2048, 4000, "256 x 128, blocked weights"),
-    (4088, 4000, "256 x 256, ragged"),
-    (4096, 4090, "256 x 256, blocked weights"),
+    (64, 33, (32, 32, 4, 1)),
+    (72, 35, (32, 32, 4, 1)),
+    (200, 65, (32, 32, 4, 1)),
+    (512, 40, (32, 32, 6, 1)),
+    (1000, 131, (32, 32, 6, 1)),
+    (1152, 240, (32, 32, 4, 1)),
+    (1000, 700, (64, 32, 5, 1)),
+    (1024, 390, (64, 32, 5, 1)),
+    (2400, 40, (64, 32, 5, 4)),
+    (2560, 50, (64, 32, 5, 4)),
+    (64, 20000, (64, 64, 4, 1)),
+    (776, 1000, (64, 64, 4, 1)),
+    (1024, 800, (64, 64, 4, 1)),
+    (776, 2600, (64, 64, 2, 1)),
+    (1152, 1900, (64, 64, 2, 1)),
+    (1224, 2570, (128, 128, 3, 1)),
+    (1280, 2570, (128, 128, 3, 1)),
+    (520, 8010, (128, 128, 2, 1)),
+    (512, 8510, (128, 128, 2, 1)),
+    (1032, 8010, (256, 128, 3, 1)),
+    (2048, 4000, (256, 128, 3, 1)),
+    (4088, 4000, (256, 256, 2, 1)),
+    (4096, 4090, (256, 256, 2, 1)),
 ]
 
 
-@pytest.mark.parametrize("width,batch,plan", SHAPES)
+@pytest.mark.parametrize("width,batch,plan", SHAPES, ids=["%dx%d-%dx%d-ring%d-split%d" % (w, b, *p) for w, b, p in SHAPES])
 def test_linear_layer(width, batch, plan):
     log(f"linear {batch} x {width} x {width}: {plan}")
     m = synth.mlp(1, width, "bf16", "none", seed=900 + width, bias_std=0.5)
