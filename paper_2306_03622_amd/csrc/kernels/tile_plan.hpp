@@ -36,8 +36,13 @@ struct TileShape {
 // more whose tiles leave CUs idle are split, each split keeping 9 stages: 64 x 32 tiles from 64 of
 // them, up to 448 workgroups (392 x 512 x 4608 [104, 4 splits] 12.3, unsplit 32 x 32 14.7), else
 // 32 x 32, up to 256 (49 x 512 x 4608 [32, 8 splits] 7.3, unsplit 16; 196 x 256 x 2304 [56, 4
-// splits] 6.9, unsplit 7.6). Not a contraction with a row LayerNorm: 128 x 768 x 3072 [96] 8.0
-// unsplit, 8.6 split.
+// splits] 6.9, unsplit 7.6). With a row LayerNorm, which rides on the reduction where the width allows, 32 x 32 tiles
+// are split alike (warm passes of three encoder layers, split / unsplit, features x rows x k [tiles]: 64 x 64 x 16384
+// [4] 83 / 158, 256 x 128 x 8192 [32] 87 / 126, 768 x 128 x 3072 [96] 103 / 107, 192 x 512 x 2304 [96] 96.6 / 98.2), but
+// 64 x 32 tiles, of which each split leaves more to reduce, only from 96 stages on, and from 256 where they are more
+// than 96 (512 x 256 x 6144 [64] 112 / 124, x 3072 101 / 104, 64 x 2048 x 3072 [64] 123 / 120; 384 x 512 x 6144 [96]
+// 133 / 137, x 3072 121 / 120; 64 x 4096 x 6144 [128] 178 / 166, x 16384 297 / 295, 1024 x 256 x 6144 [128] 141 / 139, x
+// 16384 189 / 206).
 struct TilePlan {
   int bn, bm, ring, splits;
 };
@@ -79,11 +84,12 @@ inline TilePlan plan_tiles(const TileShape& s, size_t scratch_bytes) {
     return {64, 64, tiles(64, 64) <= 512 ? 4 : 2, deep_conv ? 2 : 1};
   }
   if (tiles(64, 32) >= 176) return {64, 32, 5, 1};
-  if (nst >= 36 && !s.ln) {
+  if (nst >= 36) {
     const bool wide = tiles(64, 32) >= 64;
     const long nt = wide ? tiles(64, 32) : tiles(32, 32);
     const int z = (int)std::min<long>({(wide ? 448 : 256) / nt, nst / 9, most});
-    if (z > 1) return wide ? TilePlan{64, 32, 5, z} : TilePlan{32, 32, 6, z};
+    const bool pays = !(s.ln && wide) || nst >= (nt <= 96 ? 96 : 256);
+    if (z > 1 && pays) return wide ? TilePlan{64, 32, 5, z} : TilePlan{32, 32, 6, z};
   }
   return {32, 32, tiles(32, 32) <= 256 && nst >= 8 ? 6 : 4, 1};
 }

@@ -18,16 +18,18 @@ def test_bert_small(seq, batch):
     rt.close()
 
 
-@pytest.mark.parametrize("d", [128, 256, 512])
-def test_bert_split_reduction_with_layernorm(d):
-    # FFN2 (K = 2048: 32 k-stages over 2 x d/64 tiles) is split over k here, so the second
-    # LayerNorm of each layer runs with its reduction: in registers for widths 256 and 512,
-    # as the plain reduction followed by a LayerNorm launch for width 128. Cold and warm
-    # requests agree bitwise; both match the oracle.
-    m = synth.bert(seed=45, layers=2, d=d, heads=d // 64, ffn=2048, seq=64, vocab=500, maxpos=64)
-    ids = synth.bert_input(2, 46, seq=64, vocab=500)
-    rt, (mid,) = make_runtime([m], batch_max=2)
-    log(f"bert d {d}: split FFN2 with LayerNorm")
+# (d, ffn, sequence, batch): FFN2 (ffn stages of 64 over few tiles) is split over k in all, so the second LayerNorm of a
+# layer runs with its reduction, in registers, for widths of a multiple of 256, as the plain reduction followed
+# by a LayerNorm launch for others; 32 x 32 tiles with 2 to 28 splits, then 64 x 32 tiles with 7 and 4
+@pytest.mark.parametrize("d,ffn,seq,batch", [(128, 2304, 64, 2), (256, 2304, 64, 2), (512, 4096, 64, 2), (768, 3072, 64, 2),
+                                             (256, 16384, 32, 2), (64, 16384, 64, 1), (256, 6144, 256, 2),
+                                             (192, 6152, 256, 4)])
+def test_bert_split_reduction_with_layernorm(d, ffn, seq, batch):
+    # Cold and warm requests agree bitwise; both match the oracle.
+    m = synth.bert(seed=45, layers=2, d=d, heads=d // 64, ffn=ffn, seq=seq, vocab=500, maxpos=seq)
+    ids = synth.bert_input(batch, 46, seq=seq, vocab=500)
+    rt, (mid,) = make_runtime([m], batch_max=batch)
+    log(f"bert d {d} ffn {ffn}, {batch} x {seq}: split FFN2 with LayerNorm")
     cold = infer(rt, mid, m, ids)
     assert np.array_equal(cold, infer(rt, mid, m, ids))
     check_parity(cold, m, ids, 2e-2)

@@ -58,6 +58,16 @@ def test_the_gpu_test_covers_the_tiles_it_names(plan):
         assert {p[:3] for (w, _, _), p in zip(SHAPES, got) if (w % 128 == 0) == packed} == named
 
 
+def test_deep_contractions_are_split_with_and_without_a_layernorm(plan):
+    # FFN2 of an encoder layer: few tiles and a deep k; shallower ones and many tiles stay whole
+    want = [((128, 768, 3072), (32, 32, 6, 2)), ((64, 64, 16384), (32, 32, 6, 28)), ((128, 512, 4096), (32, 32, 6, 4)),
+            ((128, 512, 2048), (32, 32, 6, 1)), ((512, 256, 6144), (64, 32, 5, 7)), ((512, 256, 3072), (32, 32, 6, 1)),
+            ((256, 1024, 16384), (64, 32, 5, 3)), ((1024, 768, 3072), (64, 64, 4, 1))]
+    assert plan([(m, n, k, 0, 0, 1, SCRATCH) for (m, n, k), _ in want]) == [p for _, p in want]
+    assert all(p[3] == 1 for p in plan([(m, n, k, 0, 0, 1, 0) for (m, n, k), _ in want]))        # no scratch
+    assert plan([(64, 64, 16384, 0, 0, 0, SCRATCH)]) == [(32, 32, 6, 28)]
+
+
 def test_every_plan_is_built_and_in_bounds(plan):
     rng = random.Random(3)
     log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
