@@ -32,10 +32,19 @@ __device__ __forceinline__ typename EpRun<R>::Raw ep_run_load(__amdgpu_buffer_rs
 // is wave-uniform). In assembly because the compiler, which knows the builtin as a write to
 // LDS, waits for every such load in flight before each LDS read that follows in program order:
 // the ring below then hides nothing (~0.47 us a stage whatever the tile and the ring's depth,
-// against 0.12 us). No register is written; the waits are lds_wait_barrier's.
+// against 0.12 us). No register is written but m0, the LDS base; the waits are lds_wait_barrier's.
+// OPERAND: m0 is an operand that the compiler sets, else the block sets it (the s_nop is the wait state between
+// that and the load either way). The compiler's schedules differ: small row-major tiles lose up to 1.1% where the
+// block sets it (1024 x 4096 encoder, 1024 rows), ResNet-50 at batch 32, of large tiles and convolutions, 0.8% where
+// the compiler does.
+template <bool OPERAND>
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint32_t dst, uint32_t voff, int soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               ::"s"(dst), "v"(voff), "s"(r), "s"(soff) : "m0");
+  if constexpr (OPERAND)
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 ::"{m0}"(dst), "v"(voff), "s"(r), "s"(soff));
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 ::"s"(dst), "v"(voff), "s"(r), "s"(soff) : "m0");
 }
 
 // Waits until at most N of this wave's vector-memory operations are in flight and its LDS reads
@@ -87,6 +96,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
   constexpr int PER = (LPS + SP - 1) / SP;             // loads per group
   constexpr int RUN = PAIR ? 8 : 4, NR = NB * 4 / RUN; // outputs per run, runs per lane and row block
   constexpr bool EPF = VEC && NR * MB <= 4;
+  constexpr bool M0_OPERAND = MODE == X_ROWS && BN <= 64;
   static_assert(BN % (8 * NW) == 0 && BM % (8 * NW) == 0 && WN % 16 == 0 && WM % 16 == 0 && NB % IG == 0 &&
                     NST >= 2 && NST <= 8 && (VEC || !PAIR), "tile shape");
   constexpr int ABYTES = BN * 128, SBYTES = (BN + BM) * 128;
@@ -173,15 +183,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
     for (int u = 0; u < LPS; ++u) {
       if (u < lo || u >= hi) continue;
       if (u < TA) {
-        lds_load16(rw, dst + (wave * TA + u) * 1024, (ta[u] & edge) ? kOffNone : offa[u], sl * (PK ? 2048 : 128));
+        lds_load16<M0_OPERAND>(rw, dst + (wave * TA + u) * 1024, (ta[u] & edge) ? kOffNone : offa[u], sl * (PK ? 2048 : 128));
       } else {
         const int t = u - TA;
         const uint32_t d = dst + ABYTES + (wave * TB + t) * 1024;
         if constexpr (MODE == X_ROWS) {
-          lds_load16(rx, d, (tb & edge) ? kOffNone : offb[t], sl * 128);
+          lds_load16<M0_OPERAND>(rx, d, (tb & edge) ? kOffNone : offb[t], sl * 128);
         } else {
           const bool ok = ((unsigned)(ih0[t] + kh) < (unsigned)a.H) & ((unsigned)(iw0[t] + kw) < (unsigned)a.W);
-          lds_load16(rx, d, ok ? offb[t] + (uint32_t)(((kh * a.W + kw) * a.C + c0) * 2) : kOffNone, 0);
+          lds_load16<M0_OPERAND>(rx, d, ok ? offb[t] + (uint32_t)(((kh * a.W + kw) * a.C + c0) * 2) : kOffNone, 0);
         }
       }
     }
