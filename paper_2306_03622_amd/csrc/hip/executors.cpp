@@ -38,7 +38,7 @@ hipError_t run_mlp(ExecCtx& x) {
     const int a = last ? k::ACT_NONE : act;
     if (f32) {
       TP_TRY(k::linear_f32(static_cast<const float*>(cur), B, W, x.t<float>(l, TP_ROLE_W), W,
-                           x.t<float>(l, TP_ROLE_B), a, static_cast<float*>(dst), x.stream));
+                           x.t<float>(l, TP_ROLE_B), a, static_cast<float*>(dst), x.far(), x.stream));
     } else {
       k::Epilogue ep;
       ep.bias = x.t<uint16_t>(l, TP_ROLE_B);
@@ -46,6 +46,7 @@ hipError_t run_mlp(ExecCtx& x) {
       ep.out = dst;
       ep.out_f32 = last;
       ep.w_packed = s.packed_mlp;
+      ep.w_far = x.far();
       TP_TRY(k::linear_bf16(static_cast<const uint16_t*>(cur), B, W, x.t<uint16_t>(l, TP_ROLE_W), W, ep, x.split,
                              x.stream));
     }
@@ -73,7 +74,7 @@ hipError_t run_mlp_swapin(ExecCtx& x, const void* host_image) {
     const bool last = l == L - 1;
     dst = last ? x.out : buf[l & 1];
     TP_TRY(k::linear_f32(static_cast<const float*>(cur), B, W, x.t<float>(l, TP_ROLE_W), W, x.t<float>(l, TP_ROLE_B),
-                         last ? k::ACT_NONE : act, static_cast<float*>(dst), x.stream));
+                         last ? k::ACT_NONE : act, static_cast<float*>(dst), x.far(), x.stream));
     cur = dst;
   }
   return hipSuccess;
@@ -98,6 +99,7 @@ hipError_t run_resnet(ExecCtx& x) {
     ep.res = res;
     ep.act = act;
     ep.out = out;
+    ep.w_far = x.far();
     return k::conv_bf16(in, B, c.hin, c.hin, c.c.cin, x.t<uint16_t>(layer, TP_ROLE_W), c.c.cout, c.c.k, c.c.k,
                         c.c.stride, c.c.pad, ep, x.split, x.stream);
   };
@@ -125,6 +127,7 @@ hipError_t run_resnet(ExecCtx& x) {
         e0.out = buf[o[0]];
         e1.bias = x.t<uint16_t>(li + 3, TP_ROLE_B);
         e1.out = buf[o[2]];
+        e0.w_far = e1.w_far = x.far();
         TP_TRY(k::conv1x1_pair(buf[cur], B, c0.hin, c0.hin, c0.c.cin, x.t<uint16_t>(li, TP_ROLE_W), c0.c.cout, e0,
                                x.t<uint16_t>(li + 3, TP_ROLE_W), c1.c.cout, c1.c.stride, e1, &paired, x.stream));
       }
@@ -147,6 +150,7 @@ hipError_t run_resnet(ExecCtx& x) {
   ep.bias = x.t<uint16_t>(li, TP_ROLE_B);
   ep.out = x.out;
   ep.out_f32 = 1;
+  ep.w_far = x.far();
   return k::linear_bf16(pooled, B, 2048, x.t<uint16_t>(li, TP_ROLE_W), classes, ep, x.split, x.stream);
 }
 
@@ -174,11 +178,13 @@ hipError_t run_bert(ExecCtx& x) {
   for (int l = 1; l <= L; ++l) {
     TP_TRY(x.wait->need(l));
     k::Epilogue e1;
+    e1.w_far = x.far();
     e1.bias = x.t<uint16_t>(l, TP_ROLE_QKV_B);
     e1.out = qkv;
     TP_TRY(k::linear_bf16(h, M, d, x.t<uint16_t>(l, TP_ROLE_QKV_W), 3 * d, e1, x.split, x.stream));
     TP_TRY(k::attention(qkv, B, S, H, att, x.stream));
     k::Epilogue e2;
+    e2.w_far = x.far();
     e2.bias = x.t<uint16_t>(l, TP_ROLE_O_B);
     e2.res = h;
     e2.out = pre;
@@ -189,11 +195,13 @@ hipError_t run_bert(ExecCtx& x) {
     e2.ln_out = h;
     TP_TRY(k::linear_bf16(att, M, d, x.t<uint16_t>(l, TP_ROLE_O_W), d, e2, x.split, x.stream));
     k::Epilogue e3;
+    e3.w_far = x.far();
     e3.bias = x.t<uint16_t>(l, TP_ROLE_FFN1_B);
     e3.act = k::ACT_GELU;
     e3.out = ff;
     TP_TRY(k::linear_bf16(h, M, d, x.t<uint16_t>(l, TP_ROLE_FFN1_W), F, e3, x.split, x.stream));
     k::Epilogue e4;
+    e4.w_far = x.far();
     e4.bias = x.t<uint16_t>(l, TP_ROLE_FFN2_B);
     e4.res = h;
     e4.out = pre;

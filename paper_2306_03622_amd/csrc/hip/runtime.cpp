@@ -296,6 +296,19 @@ constexpr size_t kGraphs = 4;
 // one), so only forward passes of at least this many kernels are replayed as graphs.
 constexpr int kGraphMinLaunches = 16;
 
+// A graph captured over weights in host memory also serves the model in device memory, so it holds the tile order of
+// the latter. Up to 8 tile rows of 32 that order is the same; from there on each XCD would read all weights over the
+// link (three encoder layers of 128, 2048 rows: 290 us with the graph, launched one by one 178).
+constexpr long kFarRows = 256;
+
+long forward_rows(const ModelSpec& s, int batch) {
+  switch (s.arch) {
+    case TP_ARCH_MLP: return batch;
+    case TP_ARCH_BERT: return (long)batch * s.dims[4];
+    default: return (long)batch * s.dims[1] * s.dims[1] / 16;      // ResNet-50's first blocks
+  }
+}
+
 int forward_launches(const ModelSpec& s) {
   switch (s.arch) {
     case TP_ARCH_MLP: return s.dims[0];
@@ -555,8 +568,10 @@ tp_status infer_request(tp_ctx* c, int32_t id, const void* input_dev, int32_t ba
   if (!swapped && allow_touch) maybe_touch(c, m, off);
   c->last_served = id;
   m->touch_due = false;          // this request reads the weights (a cold one as they land)
+  // (a direct-access request of many rows takes kernels of its own, launched one by one)
   const bool graphs = allow_graphs && !(c->cfg.flags & TP_FLAG_NO_GRAPH) && !m->graph_failed &&
-                      forward_launches(m->spec) >= kGraphMinLaunches;
+                      forward_launches(m->spec) >= kGraphMinLaunches &&
+                      !(direct && swapped && forward_rows(m->spec, batch) > kFarRows);
   // a swapping request's kernels run on the library's execution stream (see tp_create),
   // all but its last chunk's (a single-chunk request stays on the caller's stream)
   const bool forked = swapped && !direct && c->exec && m->chunks.size() > 1;

@@ -119,6 +119,8 @@ struct ExecCtx {
   const T* t(uint32_t layer, uint32_t role) const {
     return reinterpret_cast<const T*>(base + m->spec.t(layer, role).offset);
   }
+  // weights read over the host link (not while a graph is captured, which outlives their stay there)
+  bool far() const { return base == static_cast<const char*>(m->host_dev) && !k::launch_log; }
 };
 
 hipError_t run_mlp(ExecCtx& x);

@@ -17,7 +17,6 @@
 #include <algorithm>
 
 #include "gemm_tile.hpp"
-#include "tile_plan.hpp"
 
 namespace tp {
 namespace k {
@@ -102,19 +101,24 @@ hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) 
   a.splits = (nst + a.kst - 1) / a.kst;        // no empty split
   a.partials = sp.partials;
   const dim3 grid(tn * tm * a.splits), block(64 * WGN * WGM);
+  auto go = [&](auto kern) { (void)launch(kern, grid, block, 0, s, a, tn, tm); };
+  const bool far = a.ep.w_far;
   if constexpr (MODE == X_ROWS && VEC) {
     if (a.ep.w_packed) {
-      (void)launch((k_gemm<BN, BM, WGN, WGM, NST, MODE, true, MINW, true>), grid, block, 0, s, a, tn, tm);
+      far ? go(k_gemm<BN, BM, WGN, WGM, NST, MODE, true, MINW, true, true>)
+          : go(k_gemm<BN, BM, WGN, WGM, NST, MODE, true, MINW, true, false>);
       return finish(a, s);
     }
   }
-  (void)launch((k_gemm<BN, BM, WGN, WGM, NST, MODE, false, MINW, VEC>), grid, block, 0, s, a, tn, tm);
+  far ? go(k_gemm<BN, BM, WGN, WGM, NST, MODE, false, MINW, VEC, true>)
+      : go(k_gemm<BN, BM, WGN, WGM, NST, MODE, false, MINW, VEC, false>);
   return finish(a, s);
 }
 
 template <int MODE>
 hipError_t pick_tiled(const GemmArgs& a, const Split& sp, hipStream_t s) {
-  const TileShape shape{a.M, a.N, a.K, MODE == X_CONV64, a.ep.act == ACT_GELU, a.ep.ln_g != nullptr};
+  const TileShape shape{a.M, a.N, a.K, MODE == X_CONV64, a.ep.act == ACT_GELU, a.ep.ln_g != nullptr,
+                        a.ep.w_far != 0};
   const TilePlan p = plan_tiles(shape, sp.partials ? sp.partial_bytes : 0);
   // waves n x m, ring, least waves per SIMD
   if (p.bn == 256 && p.bm == 256) return launch_tiled<256, 256, 4, 2, 2, 1, MODE>(a, p.splits, sp, s);
@@ -209,8 +213,9 @@ hipError_t conv1x1_pair(const uint16_t* x, int B, int H, int W, int C, const uin
   a.splits = b.splits = 1;
   a.kst = b.kst = (C + 63) / 64;
   *done = true;
-  if (stride1 == 1) (void)launch(k_gemm_pair<X_ROWS>, dim3((unsigned)tiles), dim3(256), 0, s, a, tna, tma, b, tnb, tmb);
-  else (void)launch(k_gemm_pair<X_CONV64>, dim3((unsigned)tiles), dim3(256), 0, s, a, tna, tma, b, tnb, tmb);
+  auto go = [&](auto kern) { (void)launch(kern, dim3((unsigned)tiles), dim3(256), 0, s, a, tna, tma, b, tnb, tmb); };
+  if (stride1 == 1) a.ep.w_far ? go(k_gemm_pair<X_ROWS, true>) : go(k_gemm_pair<X_ROWS, false>);
+  else a.ep.w_far ? go(k_gemm_pair<X_CONV64, true>) : go(k_gemm_pair<X_CONV64, false>);
   return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // "B" operand 16 activation rows m.
 #pragma once
 #include "gemm_args.hpp"
+#include "tile_plan.hpp"
 
 namespace tp {
 namespace k {
@@ -84,7 +85,7 @@ __device__ __forceinline__ void lds_wait_barrier() {
 // The body of workgroup `id` of `total`; lds: gemm_lds bytes.
 constexpr size_t gemm_lds(int bn, int bm, int nst) { return (size_t)nst * (bn + bm) * 128; }
 
-template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, bool VEC>
+template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, bool VEC, bool FAR>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int id, int total, char* lds) {
   constexpr int NW = WGN * WGM;
   constexpr int TA = BN / 8 / NW, TB = BM / 8 / NW, LPS = TA + TB;   // 1 KB loads per wave and stage
@@ -106,19 +107,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
   const int wn = wave % WGN, wm = wave / WGN;
   const int r = lane & 15, q = lane >> 4;
 
-  // The tile of this workgroup. Workgroups go to the 8 XCDs in turn, each with an L2 of its own:
-  // XCD x takes the x-th contiguous eighth of the tiles, which are ordered in bands of kBand
-  // tile rows, so the tiles an XCD works on at a time share their operands' rows.
-  constexpr int kBand = 8;
-  {
-    const int per = total >> 3, rem = total & 7, xcd = id & 7;
-    id = xcd * per + min(xcd, rem) + (id >> 3);
-  }
-  const int z = a.splits > 1 ? id / (tn * tm) : 0;
-  id -= z * tn * tm;
-  const int band = id / (kBand * tn), first = band * kBand, height = min(kBand, tm - first);
-  const int in = id - first * tn, tx = in / height;
-  const int n_base = tx * BN, m_base = (first + in - tx * height) * BM;
+  const TileAt at = tile_at<FAR>(id, total, tn, tm, a.splits);
+  const int z = at.z, n_base = at.tx * BN, m_base = at.ty * BM;
   const int nst = (a.K + 63) >> 6, full = a.K >> 6;
   const int s0 = z * a.kst;
   const int n = min(s0 + a.kst, nst) - s0;      // stages of this split (>= 1: no empty split)
@@ -363,20 +353,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
   }
 }
 
-template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, int MINW, bool VEC>
+template <int BN, int BM, int WGN, int WGM, int NST, int MODE, bool PK, int MINW, bool VEC, bool FAR>
 __global__ __launch_bounds__(64 * WGN * WGM, MINW) void k_gemm(GemmArgs a, int tn, int tm) {
   __shared__ __attribute__((aligned(1024))) char lds[gemm_lds(BN, BM, NST)];
-  gemm_tile<BN, BM, WGN, WGM, NST, MODE, PK, VEC>(a, tn, tm, blockIdx.x, gridDim.x, lds);
+  gemm_tile<BN, BM, WGN, WGM, NST, MODE, PK, VEC, FAR>(a, tn, tm, blockIdx.x, gridDim.x, lds);
 }
 
 // Two independent contractions in one launch, 32 x 32 tiles: workgroups [0, na) the first, the others the
 // second. The same sums in the same order as in launches of their own with any tile (unsplit), so the same bits. Its rule: conv1x1_pair.
-template <int MODE_B>
+template <int MODE_B, bool FAR>
 __global__ __launch_bounds__(256, 3) void k_gemm_pair(GemmArgs a, int tna, int tma, GemmArgs b, int tnb, int tmb) {
   __shared__ __attribute__((aligned(1024))) char lds[gemm_lds(32, 32, 6)];
   const int na = tna * tma;
-  if ((int)blockIdx.x < na) gemm_tile<32, 32, 2, 2, 6, X_ROWS, false, true>(a, tna, tma, blockIdx.x, na, lds);
-  else gemm_tile<32, 32, 2, 2, 6, MODE_B, false, true>(b, tnb, tmb, blockIdx.x - na, gridDim.x - na, lds);
+  if ((int)blockIdx.x < na) gemm_tile<32, 32, 2, 2, 6, X_ROWS, false, true, FAR>(a, tna, tma, blockIdx.x, na, lds);
+  else gemm_tile<32, 32, 2, 2, 6, MODE_B, false, true, FAR>(b, tnb, tmb, blockIdx.x - na, gridDim.x - na, lds);
 }
 
 }  // namespace k

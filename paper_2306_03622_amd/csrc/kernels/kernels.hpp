@@ -35,6 +35,7 @@ struct Epilogue {
   const uint16_t* bias = nullptr;   // bf16 [N], may be null
   const void* res = nullptr;        // bf16 [M][N], may be null
   int act = 0;                      // ACT_*
+  int w_far = 0;                    // weights in host memory (other tiles and order, the same results)
   void* out = nullptr;
   int out_f32 = 0;                  // out dtype: 0 bf16, 1 fp32
   int w_packed = 0;                 // weights in 16 x 128 blocks (N % 16 == 0, K % 128 == 0)
@@ -79,9 +80,9 @@ hipError_t conv1x1_pair(const uint16_t* x, int B, int H, int W, int C, const uin
 hipError_t stem_pool(const uint16_t* x, int B, int H, int W, const uint16_t* w, const uint16_t* bias, uint16_t* y,
                      hipStream_t s);
 
-// fp32 linear: y[M][N] = act(x[M][K] * w[N][K]^T + bias). K % 4 == 0.
+// fp32 linear: y[M][N] = act(x[M][K] * w[N][K]^T + bias). K % 4 == 0. w_far: as in Epilogue.
 hipError_t linear_f32(const float* x, int M, int K, const float* w, int N, const float* bias, int act, float* y,
-                      hipStream_t s);
+                      bool w_far, hipStream_t s);
 
 // Row LayerNorm of fp32 x[M][D] (population variance) with bf16 gamma/beta; out bf16 or
 // fp32. D % 64 == 0, D <= 1024.

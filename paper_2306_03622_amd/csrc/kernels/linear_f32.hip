@@ -50,13 +50,18 @@ __global__ __launch_bounds__(256) void k_linear_f32(const float* __restrict__ x,
 // 1000 x 1000 with the weights in the caches, this one 5.3 us; 1024 wide, 5 rows 5.2 against
 // 4.8 us.
 // SWAP: W lies in pinned host memory and is written to w_dev as it is read (see below).
+// STAGE: W lies in pinned host memory: a wave's next 8 chunks of the 16 rows are read as runs of 512 bytes, 8 loads in
+// flight, and turned into operands through LDS (in the runs of 64 bytes above the host link carried less: 2 x 1000 of 9
+// rows 215 us, 184 so, 2 x 2000 of 12 787 and 659). The same sums, so the same bits.
 constexpr int kMmWaves = 8;
 
-template <int MT, int U, bool SWAP>
+template <int MT, int U, bool SWAP, bool STAGE>
 __device__ __forceinline__ void linear_f32_tile(const float* __restrict__ x, int M, int K, const float* __restrict__ w,
                                                 int N, const float* __restrict__ bias, int act,
                                                 float* __restrict__ y, float* __restrict__ w_dev, int n0, int m0) {
   __shared__ f32x4 red[kMmWaves][MT][64];
+  __shared__ __align__(16) float wst[STAGE ? kMmWaves : 1][STAGE ? 16 : 1][8 * 16 + 4];
+  static_assert(!STAGE || 8 % U == 0, "whole rounds of a stage");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
   const bool nvalid = n0 + r < N;
@@ -74,12 +79,26 @@ __device__ __forceinline__ void linear_f32_tile(const float* __restrict__ x, int
   const int c_end = min(nc, (wave + 1) * per);
   for (int c0 = wave * per; c0 < c_end; c0 += U) {
     float4 a[U], b[U][MT];
+    const int at = (c0 - wave * per) & 7;        // chunk of the stage
+    if (STAGE && at == 0) {
+      float4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int row = 2 * i + (lane >> 5), k = c0 * 16 + (lane & 31) * 4;
+        const bool in = k < min(c_end * 16, K);
+        v[i] = *reinterpret_cast<const float4*>(w + (size_t)min(n0 + row, N - 1) * K + (in ? k : 0));
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        *reinterpret_cast<float4*>(&wst[wave][2 * i + (lane >> 5)][(lane & 31) * 4]) = v[i];
+      __builtin_amdgcn_wave_barrier();           // a wave's LDS operations take effect in order
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = (c0 + u) * 16 + q * 4;
       const bool in = c0 + u < c_end && k < K;
       const int kk = in ? k : 0;
-      a[u] = *reinterpret_cast<const float4*>(wr + kk);
+      a[u] = *reinterpret_cast<const float4*>(STAGE ? &wst[wave][r][(at + u) * 16 + q * 4] : wr + kk);
       if (SWAP && in && nvalid) *reinterpret_cast<float4*>(w_dev + (size_t)(n0 + r) * K + kk) = a[u];
 #pragma unroll
       for (int t = 0; t < MT; ++t) b[u][t] = *reinterpret_cast<const float4*>(xr[t] + kk);
@@ -133,8 +152,9 @@ constexpr int kMmU = 2;      // chunks in flight per wave from device memory (4 
 
 constexpr int kMmY = 65536;  // the most row blocks a grid's y takes
 
-// Z: the row blocks continue in the grid's z (always, it cost 4 x 1000 at batch 64 28.0 -> 28.6 us).
-template <int MT, bool Z = false>
+// Z: the row blocks continue in the grid's z (always, it cost 4 x 1000 at batch 64 28.0 -> 28.6 us). STAGE:
+// weights in host memory.
+template <int MT, bool Z = false, bool STAGE = false>
 __global__ __launch_bounds__(64 * kMmWaves) void k_linear_f32_mm(const float* __restrict__ x, int M, int K,
                                                                  const float* __restrict__ w, int N,
                                                                  const float* __restrict__ bias, int act,
@@ -142,9 +162,9 @@ __global__ __launch_bounds__(64 * kMmWaves) void k_linear_f32_mm(const float* __
   if constexpr (Z) {
     const long m0 = ((long)blockIdx.z * kMmY + blockIdx.y) * 16 * MT;
     if (m0 >= M) return;
-    linear_f32_tile<MT, kMmU, false>(x, M, K, w, N, bias, act, y, nullptr, blockIdx.x * 16, (int)m0);
+    linear_f32_tile<MT, kMmU, false, STAGE>(x, M, K, w, N, bias, act, y, nullptr, blockIdx.x * 16, (int)m0);
   } else {
-    linear_f32_tile<MT, kMmU, false>(x, M, K, w, N, bias, act, y, nullptr, blockIdx.x * 16, blockIdx.y * 16 * MT);
+    linear_f32_tile<MT, kMmU, false, STAGE>(x, M, K, w, N, bias, act, y, nullptr, blockIdx.x * 16, blockIdx.y * 16 * MT);
   }
 }
 
@@ -177,7 +197,7 @@ __global__ __launch_bounds__(MM ? 64 * kMmWaves : 256) void k_linear_f32_swap(co
   if ((int)blockIdx.x < cwg) {
     if constexpr (MM) {
       // all of a row's chunks in flight (K <= 1024): the round trip over the host link is what counts
-      linear_f32_tile<1, 8, true>(x, M, K, w_host, N, bias_host, act, y, w_dev, blockIdx.x * 16, 0);
+      linear_f32_tile<1, 8, true, false>(x, M, K, w_host, N, bias_host, act, y, w_dev, blockIdx.x * 16, 0);
       return;
     }
     const int lane = threadIdx.x & 63;
@@ -264,7 +284,7 @@ hipError_t linear_f32_swap(const float* x, int M, int K, int N, int act, float* 
 }
 
 hipError_t linear_f32(const float* x, int M, int K, const float* w, int N, const float* bias, int act, float* y,
-                      hipStream_t s) {
+                      bool w_far, hipStream_t s) {
   if (!x || !w || !y || M < 1 || N < 1 || K < 4 || (K & 3) || act < 0 || act > 2) return hipErrorInvalidValue;
   if (M < kMmRows) {
     (void)launch(k_linear_f32, dim3((N + 3) / 4), dim3(256), 0, s, x, M, K, w, N, bias, act, y);
@@ -276,10 +296,18 @@ hipError_t linear_f32(const float* x, int M, int K, const float* w, int N, const
   const long nt = (N + 15) / 16, tiles = nt * (((long)M + 15) / 16);
   auto go = [&](auto kern, int rows) {
     const long blocks = ((long)M + rows - 1) / rows;
-    const dim3 grid((unsigned)nt, (unsigned)std::min<long>(blocks, kMmY), (unsigned)((blocks + kMmY - 1) / kMmY));
+    // Weights in host memory: as few row blocks as there may be, and a multiple of the 8 XCDs in x (tiles beyond N
+    // store nothing), which puts all row blocks of a feature tile on one XCD, so that they share one read of its weights
+    // over the link (2 x 1000 read in place, 64 rows 762 us without, 196 so, 256 rows 779 and 196).
+    const bool pad = w_far && blocks > 1;
+    const dim3 grid((unsigned)(pad ? (nt + 7) / 8 * 8 : nt), (unsigned)std::min<long>(blocks, kMmY),
+                    (unsigned)((blocks + kMmY - 1) / kMmY));
     (void)launch(kern, grid, dim3(64 * kMmWaves), 0, s, x, M, K, w, N, bias, act, y);
   };
-  if (tiles <= 384 || M <= 16) go(k_linear_f32_mm<1>, 16);
+  if (w_far && M <= 16) go((k_linear_f32_mm<1, false, true>), 16);
+  else if (w_far && M <= 32) go((k_linear_f32_mm<2, false, true>), 32);
+  else if (w_far && M <= 64L * kMmY) go((k_linear_f32_mm<4, false, true>), 64);
+  else if (tiles <= 384 || M <= 16) go(k_linear_f32_mm<1>, 16);
   else if (tiles <= 768 || M <= 32) go(k_linear_f32_mm<2>, 32);
   else if (M <= 64L * kMmY) go(k_linear_f32_mm<4>, 64);
   else go((k_linear_f32_mm<4, true>), 64);

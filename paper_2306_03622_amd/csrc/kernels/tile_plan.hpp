@@ -1,16 +1,55 @@
-// Which tiles a bf16 contraction takes (host code only, no HIP).
+// Which tiles a bf16 contraction takes, and in which order (no HIP headers: also compiled for the host alone).
 #pragma once
 #include <algorithm>
 #include <cstddef>
 
+#ifdef __HIPCC__
+#define TP_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define TP_HOST_DEVICE inline
+#endif
+
 namespace tp {
 namespace k {
 
+// The tile (tx of tn, of features; ty of tm, of rows; k split z) that workgroup `id` of `total` = tn tm splits computes.
+// Workgroups go to the 8 XCDs in turn, each with an L2 of its own: XCD x takes the x-th contiguous eighth of
+// the tiles. Those are ordered in bands of kBand tile rows, so that the tiles an XCD works on at a time share their
+// operands' rows. With weights in host memory (FAR) all rows are one band: an XCD then reads an
+// eighth of the weights over the host link, instead of each XCD all of them (a first request of 1000 rows
+// to a 2 x 512 model that is read in place: 58 us, in bands 106; four layers of 1024 at 300 rows 230, 332).
+constexpr int kBand = 8;
+
+struct TileAt {
+  int tx, ty, z;
+};
+
+// FAR is a template argument because a choice in the kernel cost its start: ResNet-50 1% (a branch) to 2% (a variable
+// band height, whose divisions take longer) at any batch.
+template <bool FAR>
+TP_HOST_DEVICE TileAt tile_at(int id, int total, int tn, int tm, int splits) {
+  const int per = total >> 3, rem = total & 7, xcd = id & 7;
+  id = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3);
+  TileAt t;
+  t.z = splits > 1 ? id / (tn * tm) : 0;
+  id -= t.z * tn * tm;
+  if (FAR) {
+    t.tx = id / tm;
+    t.ty = id - t.tx * tm;
+    return t;
+  }
+  const int band = id / (kBand * tn), first = band * kBand, height = kBand < tm - first ? kBand : tm - first;
+  const int in = id - first * tn;
+  t.tx = in / height;
+  t.ty = first + in - t.tx * height;
+  return t;
+}
+
 // y[M][N] = x[M][K] w[N][K]^T; conv: an implicit-GEMM convolution; gelu, ln: the epilogue has a GELU, a row
-// LayerNorm follows
+// LayerNorm follows; far: the weights are read over the host link
 struct TileShape {
   int M, N, K;
-  bool conv, gelu, ln;
+  bool conv, gelu, ln, far;
 };
 
 // Tile shape (output features x rows), ring depth and k split of a tiled contraction, by how many
@@ -65,7 +104,7 @@ inline double large_tile_us(int bn, int bm, long tiles, const TileShape& s) {
   return bm == 128 ? rounds * (0.9 * nst + (s.gelu ? 8 : 2)) : rounds * (1.65 * nst + (s.gelu ? 13 : 10));
 }
 
-inline TilePlan plan_tiles(const TileShape& s, size_t scratch_bytes) {
+inline TilePlan plan_near(const TileShape& s, size_t scratch_bytes) {
   auto tiles = [&](int bn, int bm) { return (long)((s.N + bn - 1) / bn) * ((s.M + bm - 1) / bm); };
   const int nst = (s.K + 63) / 64;
   if (s.N % 8) return {32, 32, 4, 1};        // outputs in no whole vectors
@@ -92,6 +131,18 @@ inline TilePlan plan_tiles(const TileShape& s, size_t scratch_bytes) {
     if (z > 1 && pays) return wide ? TilePlan{64, 32, 5, z} : TilePlan{32, 32, 6, z};
   }
   return {32, 32, tiles(32, 32) <= 256 && nst >= 8 ? 6 : 4, 1};
+}
+
+// With the weights in host memory and fewer columns of tiles than XCDs, several XCDs read the same weights over the link:
+// 32 x 32 tiles then, which add their sums in the same order, for weights of 256 KB and more and up to 2048 of
+// them (read in place, us with the tiles above / these: ResNet-50 at 224 x 224, batch 8 2190 / 1782, 12 2116 / 1882, 32 2475 /
+// 2370; beyond, two encoder layers of 768 at 8192 rows, 6144 tiles, 1913 / 2460).
+inline TilePlan plan_tiles(const TileShape& s, size_t scratch_bytes) {
+  const TilePlan p = plan_near(s, scratch_bytes);
+  const long columns = (s.N + p.bn - 1) / p.bn, small = (long)((s.N + 31) / 32) * ((s.M + 31) / 32);
+  if (s.far && p.splits == 1 && p.bn > 32 && columns < 8 && (long)s.N * s.K >= 1 << 17 && small <= 2048)
+    return {32, 32, small <= 256 ? 6 : 4, 1};
+  return p;
 }
 
 }  // namespace k
