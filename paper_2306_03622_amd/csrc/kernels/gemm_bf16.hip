@@ -23,40 +23,31 @@ namespace k {
 
 namespace {
 
-// y = epilogue(sum over splits z = 0, 1, ... of P[z]) for four consecutive outputs per thread.
-// A thread fetches the epilogue's inputs and ZG partials before it adds any (a launch that
+// y = epilogue(sum over splits z = 0, 1, ... of P[z]) for four consecutive outputs per thread (N % 8 == 0: other
+// widths are not split). A thread fetches the epilogue's inputs and ZG partials before it adds any (a launch that
 // waited for each partial in turn spent ~5 us on a few MB: one memory round trip per split);
 // the additions keep split order, so results are the same as summing one split at a time.
 template <int ZG, int RES>
 __global__ __launch_bounds__(256) void k_split_reduce(GemmArgs a) {
   const long q = (long)blockIdx.x * 256 + threadIdx.x;       // index of a group of 4 outputs
-  const int groups_per_row = (a.N + 3) >> 2;
-  const long total = (long)a.M * groups_per_row;
-  if (q >= total) return;
+  const int groups_per_row = a.N >> 2;
+  if (q >= (long)a.M * groups_per_row) return;
   const int m = (int)(q / groups_per_row), n0 = (int)(q - (long)m * groups_per_row) * 4;
   const size_t plane = (size_t)a.M * a.N, base = (size_t)m * a.N + n0;
   f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (n0 + 3 < a.N && (a.N & 3) == 0) {
-    const Ep4In in = ep4_fetch<RES>(a.ep, base, n0);
-    for (int z0 = 0; z0 < a.splits; z0 += ZG) {
-      float4 t[ZG];
+  const Ep4In in = ep4_fetch<RES>(a.ep, base, n0);
+  for (int z0 = 0; z0 < a.splits; z0 += ZG) {
+    float4 t[ZG];
 #pragma unroll
-      for (int u = 0; u < ZG; ++u)
-        if (z0 + u < a.splits) t[u] = *reinterpret_cast<const float4*>(a.partials + (z0 + u) * plane + base);
+    for (int u = 0; u < ZG; ++u)
+      if (z0 + u < a.splits) t[u] = *reinterpret_cast<const float4*>(a.partials + (z0 + u) * plane + base);
 #pragma unroll
-      for (int u = 0; u < ZG; ++u)
-        if (z0 + u < a.splits) sum += f32x4{t[u].x, t[u].y, t[u].z, t[u].w};
-    }
-    float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-    ep_apply<RES>(a.ep, in, v);
-    ep_store(a.ep, base, v);
-    return;
+    for (int u = 0; u < ZG; ++u)
+      if (z0 + u < a.splits) sum += f32x4{t[u].x, t[u].y, t[u].z, t[u].w};
   }
-  for (int z = 0; z < a.splits; ++z) {
-    const float* p = a.partials + z * plane + base;
-    for (int e = 0; e < 4 && n0 + e < a.N; ++e) sum[e] += p[e];
-  }
-  store_row4(a, m, n0, sum);
+  float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+  ep_apply<RES>(a.ep, in, v);
+  ep_store(a.ep, base, v);
 }
 
 template <int RES>
@@ -83,7 +74,7 @@ hipError_t finish(const GemmArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   if (a.splits > 1) {
     if (a.ep.ln_g && split_reduce_ln_fits(a.N)) return split_reduce_ln(a, s);
-    const long groups = (long)a.M * ((a.N + 3) / 4);
+    const long groups = (long)a.M * (a.N / 4);
     const dim3 grid((unsigned)((groups + 255) / 256)), block(256);
     launch_split_reduce(a, grid, block, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -96,6 +87,7 @@ hipError_t finish(const GemmArgs& a, hipStream_t s) {
 
 template <int BN, int BM, int WGN, int WGM, int NST, int MINW, int MODE, bool VEC = true>
 hipError_t launch_tiled(GemmArgs a, int splits, const Split& sp, hipStream_t s) {
+  if (!VEC && splits > 1) return hipErrorInvalidValue;       // partials are whole vectors
   const int tn = (a.N + BN - 1) / BN, tm = (a.M + BM - 1) / BM, nst = (a.K + 63) / 64;
   a.kst = (nst + splits - 1) / splits;
   a.splits = (nst + a.kst - 1) / a.kst;        // no empty split

@@ -81,7 +81,7 @@ __device__ __forceinline__ void lds_wait_barrier() {
 //
 // EPF: the epilogue's bias and residual are loaded before the first operands, so that their
 // round trip overlaps the main loop (small tiles; large ones have no registers to spare).
-// VEC: N is a multiple of 8 (4 for a single block per wave), runs of outputs are whole vectors.
+// VEC: N is a multiple of 8 (4 for a single block per wave), runs of outputs are whole vectors; others are not split.
 // The body of workgroup `id` of `total`; lds: gemm_lds bytes.
 constexpr size_t gemm_lds(int bn, int bm, int nst) { return (size_t)nst * (bn + bm) * 128; }
 
@@ -326,17 +326,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
         float v[RUN];
 #pragma unroll
         for (int e = 0; e < RUN; ++e) v[e] = PAIR ? acc[2 * p + (e >> 2)][jj][e & 3] : acc[p][jj][e & 3];
-        if (a.splits > 1) {
+        if (VEC && a.splits > 1) {
           // fp32 partial of this split: P[split][m][n]
           float* o = a.partials + (size_t)z * a.M * a.N + base;
-          if constexpr (VEC) {
 #pragma unroll
-            for (int e = 0; e < RUN; e += 4) *reinterpret_cast<float4*>(o + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < RUN; ++e)
-              if (nn + e < a.N) o[e] = v[e];
-          }
+          for (int e = 0; e < RUN; e += 4) *reinterpret_cast<float4*>(o + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
         } else if constexpr (VEC) {
           if constexpr (EPF) {
             in = pre[p][jj];
