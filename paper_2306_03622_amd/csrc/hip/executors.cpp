@@ -1,8 +1,10 @@
 // Forward passes of the three model families as kernel sequences on the caller's
 // stream. Every layer first asks the Waiter for the chunk holding its weights, so a
-// cold request computes layer l while later chunks are still being copied. Kernel
-// choice and launch shapes depend only on the model and the batch, never on residency
-// or extent address, so pipelined, preloaded and relocated runs are bit-identical.
+// cold request computes layer l while later chunks are still being copied. The order in which
+// every output is summed depends only on the model and the batch, never on residency or
+// extent address, so pipelined, preloaded and relocated runs are bit-identical. Which launches
+// that takes may differ: a block's first 1x1 and projection share one when no swap is in flight, and
+// weights in host memory have other tiles and tile orders.
 #include <algorithm>
 
 #include "../kernels/kernels.hpp"

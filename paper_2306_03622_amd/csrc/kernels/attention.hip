@@ -5,10 +5,11 @@
 // computed as S^T = K Q^T on MFMA (A = 16 keys, B = 16 queries), so lane l holds the
 // scores of query l % 16 against keys 16 t + 4 (l / 16) + e. The softmax reductions
 // over keys therefore stay inside a lane plus two cross-lane exchanges (lanes l ^ 16,
-// l ^ 32), in fp32. The normalised probabilities, rounded to bf16, are used directly as
-// the A operand of O = P V: a 32-key MFMA k-block takes the lane's own values from two
-// consecutive score tiles, and the matching V entries are read with gfx950's transposing LDS
-// load (ds_read_b64_tr_b16) in the same key order, so no data moves between lanes.
+// l ^ 32), in fp32. The exponentials exp(s - max), rounded to bf16, are used directly as
+// the A operand of O = P V, and the output is multiplied by 1 / their fp32 sum: a 32-key MFMA
+// k-block takes the lane's own values from two consecutive score tiles, and the matching V
+// entries are read with gfx950's transposing LDS load (ds_read_b64_tr_b16) in the same key order,
+// so no data moves between lanes.
 #include "common.hpp"
 #include "kernels.hpp"
 

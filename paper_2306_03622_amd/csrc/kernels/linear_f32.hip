@@ -174,10 +174,10 @@ __global__ __launch_bounds__(64 * kMmWaves) void k_linear_f32_mm(const float* __
 constexpr int kMmRows = 5;
 
 // The first layer of an fp32 model whose weights are still in pinned host memory, fused with
-// the model's swap-in. Workgroups [0, cwg) compute y = act(x W^T + b) like k_linear_f32, one
-// wave per output feature, reading W from the host copy once (a row is held in registers for
-// every row of x, so the result is the same sequence of operations as k_linear_f32's) and
-// writing what they read to the device copy; the other workgroups copy every 16-byte vector of
+// the model's swap-in. Workgroups [0, cwg) compute y = act(x W^T + b): up to kMmRows - 1 rows like
+// k_linear_f32, one wave per output feature with its row of W held in registers for every row of
+// x, from kMmRows on (MM) as 16 x 16 tiles like k_linear_f32_mm, in either case by the same sequence of operations.
+// They read W from the host copy once and write what they read to the device copy; the other workgroups copy every 16-byte vector of
 // the image outside W's own [skip0, skip1) host -> device, each thread issuing all its loads
 // before its first store. All host reads of the model are thus in flight together.
 constexpr int kSwapMaxM = 8, kSwapMaxKV = 4;     // rows of x; float4 per lane and row of W (K <= 1024)

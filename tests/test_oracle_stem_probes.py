@@ -37,7 +37,7 @@ def short_window(axis, at, d):
     return f
 
 
-@pytest.mark.parametrize("image,rows", [(64, 2), (128, 8), (160, 7)])
+@pytest.mark.parametrize("image,rows", [(64, 2), (128, 7)])
 def test_planted_mistakes_fail(image, rows, monkeypatch):
     m = sp.model(image)
     n = len(sp.probes(image, rows))
