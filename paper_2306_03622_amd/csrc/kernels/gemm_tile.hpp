@@ -35,9 +35,9 @@ __device__ __forceinline__ typename EpRun<R>::Raw ep_run_load(__amdgpu_buffer_rs
 // the ring below then hides nothing (~0.47 us a stage whatever the tile and the ring's depth,
 // against 0.12 us). No register is written but m0, the LDS base; the waits are lds_wait_barrier's.
 // OPERAND: m0 is an operand that the compiler sets, else the block sets it (the s_nop is the wait state between
-// that and the load either way). The compiler's schedules differ: small row-major tiles lose up to 1.1% where the
-// block sets it (1024 x 4096 encoder, 1024 rows), ResNet-50 at batch 32, of large tiles and convolutions, 0.8% where
-// the compiler does.
+// that and the load either way). The compiler's schedules differ: small tiles lose up to 1.1% where the block sets
+// it (six encoder layers of 1024 x 4096, 1024 rows, 385 us against 381; ResNet-50 at batch 8 406 against 404), large ones where
+// the compiler does (ResNet-50 at batch 32 837 against 830).
 template <bool OPERAND>
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint32_t dst, uint32_t voff, int soff) {
   if constexpr (OPERAND)
@@ -97,7 +97,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int tn, int tm, int
   constexpr int PER = (LPS + SP - 1) / SP;             // loads per group
   constexpr int RUN = PAIR ? 8 : 4, NR = NB * 4 / RUN; // outputs per run, runs per lane and row block
   constexpr bool EPF = VEC && NR * MB <= 4;
-  constexpr bool M0_OPERAND = MODE == X_ROWS && BN <= 64;
+  constexpr bool M0_OPERAND = BN <= 64;
   static_assert(BN % (8 * NW) == 0 && BM % (8 * NW) == 0 && WN % 16 == 0 && WM % 16 == 0 && NB % IG == 0 &&
                     NST >= 2 && NST <= 8 && (VEC || !PAIR), "tile shape");
   constexpr int ABYTES = BN * 128, SBYTES = (BN + BM) * 128;
